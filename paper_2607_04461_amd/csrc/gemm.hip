@@ -13,8 +13,9 @@
 //     8-wave tiles' epilogues (bf16 store and GELU of 256-column tiles, residual updates, split-K
 //     partial sums) pass each wave's block through the freed LDS ring so that every global access
 //     covers whole 128-byte rows.
-//   * k_linear_valu: fp32 (or bf16) operands on the vector ALUs, 64x64 tiles; used by the fp32 mode
-//     and for shapes the MFMA tiling does not take.
+//   * k_linear_f32: fp32 operands on the matrix cores (v_mfma_f32_32x32x2_f32), 64x64 tiles or 32x32 tiles
+//     with K shared by four waves; k_linear_valu_dot for the shortest sums and k_linear_valu (64x64 tiles,
+//     vector ALUs) for buffers that are not on 16 bytes.
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -1131,10 +1132,140 @@ __global__ __launch_bounds__(256, 1) void k_linear_dma(int M, int N, int K, cons
   }
   dma_tile<EPI, TO, WTA>(M, N, K, A, Wt, e, m0, n0, smem);
 }
-// ---------------------------------------------------------------------------------- VALU path
-template <typename TI, int EPI, typename TO>
-__global__ __launch_bounds__(256) void k_linear_valu(int M, int N, int K, const TI *__restrict__ A,
-                                                     const TI *__restrict__ Wt, EpiArgs e) {
+// ---------------------------------------------------------------------------------- fp32 path
+// fp32 operands on the matrix cores (v_mfma_f32_32x32x2_f32: 256 FLOP per cycle and CU, twice what the
+// vector ALUs give).  Workgroup tiles of (32 TM WGM) x (32 TN WGN); K tiles of 32 floats, so that an LDS
+// row is the 128 bytes of the bf16 kernels, with their swizzle and their loads that write LDS themselves,
+// in a ring of NST stages filled NST - 1 tiles ahead with one barrier per K tile.  A lane reads four
+// consecutive k of one row at once (k = 8 s + 4 g .. + 3, g = lane >> 5) and spends them on four MFMAs,
+// whose two k's are then 8 s + j and 8 s + 4 + j on both operands.  As in the bf16 kernels the weights
+// are the MFMA's row operand; their rows are taken in the order that leaves a lane eight consecutive
+// columns of one output row twice per 32-column fragment.  KS > 1: KS wave groups share a tile and take
+// every K tile's chunk pairs s in turn, their sums added through LDS in group order at the end.  Bound by
+// the matrix cores (157 TFLOP/s nominal, a large library product reaches 154): 131 TFLOP/s at
+// (24960, 1536, 1536) on 64x64 tiles, five workgroups per CU.
+namespace mf32 {
+constexpr int BK = 32;
+}
+
+template <int EPI, int WGM, int WGN, int KS, int TM, int TN, int NST>
+__global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void k_linear_f32(int M, int N, int K,
+                                                                    const float *__restrict__ A,
+                                                                    const float *__restrict__ Wt, EpiArgs e,
+                                                                    int MT, int NT, int group_m) {
+  using mf::swz;
+  constexpr int BK = mf32::BK, WAVES = WGM * WGN * KS, BM = 32 * TM * WGM, BN = 32 * TN * WGN;
+  constexpr int STAGE = (BM + BN) * BK * 4;      // bytes: A rows, then W rows
+  constexpr int PER = (BM + BN) / 8 / WAVES;     // load instructions (8 rows each) per wave per K tile
+  static_assert(PER * WAVES * 8 == BM + BN, "whole load instructions per wave");
+  static_assert(KS == 1 || (KS - 1) * WGM * WGN * TM * TN * 4096 <= NST * STAGE, "partial sums fit the ring");
+  extern __shared__ __attribute__((aligned(16))) char smem32[];
+  const int lane = threadIdx.x & 63, li = lane & 31, g = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int grp = wave / (WGM * WGN), wm = wave % (WGM * WGN) / WGN, wn = wave % WGN;
+  int mt, nt;
+  mf::tile_of(blockIdx.x, MT, NT, mt, nt, group_m);
+  const int m0 = mt * BM, n0 = nt * BN;
+
+  // load x of this wave: the stage's rows 8 (PER wave + x) .. + 7, of A or of W; lane l -> row + (l >> 3),
+  // slot l & 7
+  const __amdgpu_buffer_rsrc_t rsA = epi::rsrc(A + (int64_t)m0 * K, (uint32_t)min(M - m0, BM) * (uint32_t)K * 4u);
+  const __amdgpu_buffer_rsrc_t rsW = epi::rsrc(Wt + (int64_t)n0 * K, (uint32_t)min(N - n0, BN) * (uint32_t)K * 4u);
+  uint32_t voff[PER];
+  int kc[PER];   // the lane's first column within a K tile
+#pragma unroll
+  for (int x = 0; x < PER; ++x) {
+    const int i = PER * wave + x, r = 8 * i - (i < BM / 8 ? 0 : BM) + (lane >> 3);
+    kc[x] = ((lane & 7) ^ swz(r)) << 2;
+    voff[x] = (uint32_t)(r * K + kc[x]) * 4u;
+  }
+  auto load = [&](int kt, int st) {
+#pragma unroll
+    for (int x = 0; x < PER; ++x) {
+      const int i = PER * wave + x;
+      char *dst = smem32 + st * STAGE + 8 * i * (BK * 4);
+      const uint32_t off = kt * BK + kc[x] < K ? voff[x] : epi::OUT_OF_RANGE;   // columns past K read as zero
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(i < BM / 8 ? rsA : rsW, (__attribute__((address_space(3))) void *)dst, 16,
+                                               off, kt * BK * 4, 0, 0);
+    }
+  };
+  // A fragment i: rows 32 TM wm + 32 i + li.  W fragment i: lane li = 8 a + 4 h + b takes row
+  // 16 (a / 2) + 8 h + 4 (a % 2) + b, so that output element 4 a + b of a lane is column
+  // 16 (a / 2) + 8 g + 4 (a % 2) + b.
+  const int wrow = 16 * (li >> 4) + 8 * ((li >> 2) & 1) + 4 * ((li >> 3) & 1) + (li & 3);
+  auto frag = [&](int st, int row, int s) {
+    return *reinterpret_cast<const f32x4 *>(smem32 + st * STAGE + row * (BK * 4) + (((2 * s + g) ^ swz(row)) << 4));
+  };
+  f32x16 acc[TN][TM];
+#pragma unroll
+  for (int i = 0; i < TN; ++i)
+#pragma unroll
+    for (int j = 0; j < TM; ++j)
+#pragma unroll
+      for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.f;
+
+  const int KT = (K + BK - 1) / BK;
+#pragma unroll
+  for (int t = 0; t < NST - 1; ++t)
+    if (t < KT) load(t, t);
+  int st = 0;
+  for (int kt = 0; kt < KT; ++kt) {
+    wait_tiles<PER>(min(NST - 2, KT - 1 - kt));   // tile kt has landed
+    __syncthreads();                              // for every wave; nobody reads the stage of tile kt - 1 any more
+    if (kt + NST - 1 < KT) load(kt + NST - 1, st == 0 ? NST - 1 : st - 1);
+#pragma unroll
+    for (int s = 0; s < 4 / KS; ++s) {
+      const int sp = s * KS + grp;
+      f32x4 fa[TM], fw[TN];
+#pragma unroll
+      for (int i = 0; i < TM; ++i) fa[i] = frag(st, 32 * TM * wm + 32 * i + li, sp);
+#pragma unroll
+      for (int i = 0; i < TN; ++i) fw[i] = frag(st, BM + 32 * TN * wn + 32 * i + wrow, sp);
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int i = 0; i < TN; ++i)
+#pragma unroll
+          for (int j = 0; j < TM; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fw[i][q], fa[j][q], acc[i][j], 0, 0, 0);
+    }
+    st = st + 1 == NST ? 0 : st + 1;
+  }
+  if constexpr (KS > 1) {
+    static_assert(WGM * WGN == 1, "one tile per wave group");
+    __syncthreads();   // every wave is past its last fragment reads: the ring is free
+    f32x4 *part = reinterpret_cast<f32x4 *>(smem32) + lane;
+    constexpr int FR = TN * TM * 4;   // 16-byte pieces per lane
+    if (grp > 0) {
+#pragma unroll
+      for (int x = 0; x < FR; ++x) {
+        const f32x16 &a = acc[x / (4 * TM)][x / 4 % TM];
+        part[((grp - 1) * FR + x) * 64] = f32x4{a[4 * (x & 3)], a[4 * (x & 3) + 1], a[4 * (x & 3) + 2], a[4 * (x & 3) + 3]};
+      }
+    }
+    __syncthreads();
+    if (grp > 0) return;
+#pragma unroll
+    for (int y = 0; y < KS - 1; ++y)
+#pragma unroll
+      for (int x = 0; x < FR; ++x) {
+        const f32x4 v = part[(y * FR + x) * 64];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[x / (4 * TM)][x / 4 % TM][4 * (x & 3) + q] += v[q];
+      }
+  }
+  wave_epilogue<EPI, float, 2 * TN, TM, 32, 1, true>(
+      e, M, N, m0 + 32 * TM * wm, n0 + 32 * TN * wn, li,
+      [&](int cg) { return 32 * (cg >> 1) + 16 * (cg & 1) + 8 * g; },
+      [&](int cg, int rb, int q) { return acc[cg >> 1][rb][8 * (cg & 1) + q]; });
+}
+
+// 64x64 tiles, a thread computing 4 rows x 4 columns; K in steps of 16 staged in LDS with k outermost.
+// Takes operands at any 4-byte address and outputs of any width.
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+
+template <int EPI>
+__global__ __launch_bounds__(256) void k_linear_valu(int M, int N, int K, const float *__restrict__ A,
+                                                     const float *__restrict__ Wt, EpiArgs e) {
   constexpr int T = 64, TK = 16;
   __shared__ float sA[TK][T + 4];
   __shared__ float sW[TK][T + 4];
@@ -1143,12 +1274,14 @@ __global__ __launch_bounds__(256) void k_linear_valu(int M, int N, int K, const 
   float acc[4][4] = {};
   const int lr = tid >> 2, lk = (tid & 3) * 4;  // loader: row 0..63, 4 consecutive k
   for (int k0 = 0; k0 < K; k0 += TK) {
+    const int k = k0 + lk;
+    f32x4u va = {0.f, 0.f, 0.f, 0.f}, vw = va;
+    if (m0 + lr < M && k < K) va = *reinterpret_cast<const f32x4u *>(A + (int64_t)(m0 + lr) * K + k);
+    if (n0 + lr < N && k < K) vw = *reinterpret_cast<const f32x4u *>(Wt + (int64_t)(n0 + lr) * K + k);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      int k = k0 + lk + q;
-      int ma = m0 + lr, nw = n0 + lr;
-      sA[lk + q][lr] = (ma < M && k < K) ? to_f32(A[(int64_t)ma * K + k]) : 0.f;
-      sW[lk + q][lr] = (nw < N && k < K) ? to_f32(Wt[(int64_t)nw * K + k]) : 0.f;
+      sA[lk + q][lr] = va[q];
+      sW[lk + q][lr] = vw[q];
     }
     __syncthreads();
 #pragma unroll
@@ -1170,8 +1303,40 @@ __global__ __launch_bounds__(256) void k_linear_valu(int M, int N, int K, const 
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     int m = m0 + ty * 4 + i;
-    if (m < M) epilogue4<EPI, TO>(e, m, n, acc[i][0], acc[i][1], acc[i][2], acc[i][3]);
+    if (m < M) epilogue4<EPI, float>(e, m, n, acc[i][0], acc[i][1], acc[i][2], acc[i][3]);
   }
+}
+
+// 16x16 tiles, a thread computing a quarter of K of 1 row x 4 columns straight from memory: no LDS, no
+// barrier.  For the shortest sums, where a launch is little but its load latency.
+template <int EPI>
+__global__ __launch_bounds__(256) void k_linear_valu_dot(int M, int N, int K, const float *__restrict__ A,
+                                                         const float *__restrict__ Wt, EpiArgs e) {
+  const int tid = threadIdx.x, part = tid & 3;
+  const int m = blockIdx.x * 16 + (tid >> 4), n = blockIdx.y * 16 + 4 * ((tid >> 2) & 3);
+  const bool live = m < M && n < N;   // N % 4 == 0
+  float acc[4] = {};
+  if (live) {
+    const f32x4u *a = reinterpret_cast<const f32x4u *>(A + (int64_t)m * K);
+    const f32x4u *w = reinterpret_cast<const f32x4u *>(Wt + (int64_t)n * K);
+    const int c4 = K / 4;
+#pragma unroll 4
+    for (int c = part; c < c4; c += 4) {
+      const f32x4u x = a[c];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const f32x4u y = w[j * c4 + c];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[j] = fmaf(x[q], y[q], acc[j]);
+      }
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    acc[j] += __shfl_xor(acc[j], 1, 64);
+    acc[j] += __shfl_xor(acc[j], 2, 64);
+  }
+  if (live && part == 0) epilogue4<EPI, float>(e, m, n, acc[0], acc[1], acc[2], acc[3]);
 }
 
 // Tile choice for bf16 operands.  The 256x256 kernel runs one workgroup per CU, the 128x128 kernel
@@ -1471,6 +1636,52 @@ static hipError_t launch_big(int M, int N, int K, const void *A, const void *Wt,
   return launch_mfma<8, 4, 2, 4, EPI, 1>(M, N, K, A, Wt, e, s);
 }
 
+// Kernel choice for fp32 operands, device times at (M, N, K) on MI355X.
+//   * A buffer off 16 bytes, and rows of more than 2^20 outputs (the MFMA kernels address 64 output rows
+//     with 31-bit byte offsets): k_linear_valu.
+//   * K <= 64 on at most one 16x16 tile per CU, where a launch is its load latency: k_linear_valu_dot
+//     ((2, 64, 64) 2.3 against 3.0 us on 32x32 MFMA tiles, (100, 64, 64) 3.1 against 3.6; at 304 tiles,
+//     (300, 256, 64), 3.8 against 3.6).
+//   * 32x32 tiles with K shared by four waves while they fill the chip better: their launch time goes with
+//     the number of tiles (four workgroups share a CU), that of 64x64 tiles with the whole rounds of one per
+//     CU, at 0.87 of the cost per output.  (390, 256, 704) 9 against 18 us, (512, 1536, 4096) 68 against 89,
+//     (1560, 1536, 1536) 74 against 78, (1560, 1536, 8960) 411 against 437.
+//   * Else 64x64 tiles: (1560, 8960, 1536) 351 us (122 TFLOP/s) against 370 on 32x32, (24960, 1536, 1536)
+//     899 us (131 TFLOP/s) against 1018; 128x128 and 64x128 tiles take 949 and 922 there.
+// The vector-ALU kernel took 284 us at (1560, 1536, 1536) and 3120 us at (24960, 1536, 1536).
+enum F32Tile { F32_VALU, F32_DOT, F32_SMALL, F32_MID };
+static F32Tile f32_tile(int M, int N, int K, bool aligned) {
+  // FLASHBON_LINEAR_TILE (tests and tuning): "f32:valu", "f32:dot", "f32:32x32", "f32:64x64"
+  const char *force = getenv("FLASHBON_LINEAR_TILE");
+  if (force && !strncmp(force, "f32:", 4)) {
+    if (!strcmp(force + 4, "valu")) return F32_VALU;
+    if (!strcmp(force + 4, "dot")) return F32_DOT;
+    if (!strcmp(force + 4, "32x32")) return F32_SMALL;
+    if (!strcmp(force + 4, "64x64")) return F32_MID;
+  }
+  if (!aligned || N > 1 << 20) return F32_VALU;
+  const int cus = cu_count();
+  auto tiles = [&](int64_t t) { return (M + t - 1) / t * ((N + t - 1) / t); };
+  if (K <= 64 && tiles(16) <= cus) return F32_DOT;
+  return 1.15 * (double)tiles(32) / (4 * cus) < (double)((tiles(64) + cus - 1) / cus) ? F32_SMALL : F32_MID;
+}
+
+template <int EPI, int WGM, int WGN, int KS, int TM, int TN, int NST>
+static hipError_t launch_f32(int M, int N, int K, const float *A, const float *Wt, const EpiArgs &e, hipStream_t s) {
+  constexpr int BM = 32 * TM * WGM, BN = 32 * TN * WGN;
+  constexpr size_t lds = (size_t)NST * (BM + BN) * mf32::BK * sizeof(float);
+  auto kern = k_linear_f32<EPI, WGM, WGN, KS, TM, TN, NST>;
+  static bool attr_set = false;
+  if (!attr_set) {
+    hipError_t err = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (err != hipSuccess) return err;
+    attr_set = true;
+  }
+  const int MT = (M + BM - 1) / BM, NT = (N + BN - 1) / BN;
+  hipLaunchKernelGGL(kern, dim3(MT * NT), dim3(64 * WGM * WGN * KS), lds, s, M, N, K, A, Wt, e, MT, NT, mf::GROUP_M);
+  return hipGetLastError();
+}
+
 template <int EPI>
 static hipError_t launch_epi(ActType t, int M, int N, int K, const void *A, const void *Wt,
                              const EpiArgs &e, hipStream_t s) {
@@ -1511,9 +1722,19 @@ static hipError_t launch_epi(ActType t, int M, int N, int K, const void *A, cons
     return launch_mfma<4, 4, 2, 2, EPI, 2>(M - c.rows, N, K, (const bf16 *)A + (size_t)c.rows * K, Wt,
                                            rows_from<EPI>(e, c.rows), s);
   }
-  dim3 grid((M + 63) / 64, (N + 63) / 64);
-  hipLaunchKernelGGL((k_linear_valu<float, EPI, float>), grid, dim3(256), 0, s, M, N, K,
-                     (const float *)A, (const float *)Wt, e);
+  const float *Af = (const float *)A, *Wf = (const float *)Wt;
+  const uintptr_t at = (uintptr_t)A | (uintptr_t)Wt | (uintptr_t)e.out | (uintptr_t)e.bias | (uintptr_t)e.gate |
+                       (uintptr_t)e.res_in | (uintptr_t)e.cache;
+  switch (f32_tile(M, N, K, at % 16 == 0)) {
+    case F32_MID: return launch_f32<EPI, 2, 2, 1, 1, 1, 2>(M, N, K, Af, Wf, e, s);
+    case F32_SMALL: return launch_f32<EPI, 1, 1, 4, 1, 1, 3>(M, N, K, Af, Wf, e, s);
+    case F32_DOT:
+      hipLaunchKernelGGL(k_linear_valu_dot<EPI>, dim3((M + 15) / 16, (N + 15) / 16), dim3(256), 0, s, M, N, K, Af, Wf, e);
+      break;
+    case F32_VALU:
+      hipLaunchKernelGGL(k_linear_valu<EPI>, dim3((M + 63) / 64, (N + 63) / 64), dim3(256), 0, s, M, N, K, Af, Wf, e);
+      break;
+  }
   return hipGetLastError();
 }
 
@@ -1522,7 +1743,12 @@ int describe_linear(ActType t, int epi, int M, int N, int K, char *buf, int len)
   int kernels = 1;
   auto rows_of = [](int w) { return std::to_string(32 * w); };
   if (t != ACT_BF16) {
-    d = "k_linear_valu: 64x64 tiles, fp32 vector ALUs";
+    switch (f32_tile(M, N, K, true)) {   // operands on 16 bytes
+      case F32_MID: d = "k_linear_f32: 64x64 tiles, fp32 matrix cores"; break;
+      case F32_SMALL: d = "k_linear_f32: 32x32 tiles, K over 4 waves, fp32 matrix cores"; break;
+      case F32_DOT: d = "k_linear_valu_dot: 16x16 tiles, K over 4 lanes, fp32 vector ALUs"; break;
+      case F32_VALU: d = "k_linear_valu: 64x64 tiles, fp32 vector ALUs"; break;
+    }
   } else {
     const bool dma_ok = epi != EPI_EULER && K % mf::BK == 0 && K >= 2 * mf::BK && N % 8 == 0;
     TileChoice c = pick_tiles(M, N, K, dma_ok);
