@@ -1,8 +1,10 @@
 // Softmax attention of the DiT block: self-attention over image tokens and cross-attention to the
 // candidate's prompt tokens, softmax(q k^T / sqrt(dh)) v per (candidate, head).
+//   * k_attn_f32: every product and sum in fp32 on the matrix cores (v_mfma_f32_32x32x2_f32); fp32 operands of
+//     any head dim, bf16 operands of head dims below 128.
 //   * k_attn_valu: one lane per query, online softmax over 16-key sub-tiles staged in LDS as fp32;
-//     any head_dim <= 128 (multiple of 8); fp32 or bf16 operands.  Used by the fp32 mode and for
-//     head dims the MFMA kernel does not take.
+//     any head_dim <= 128 (multiple of 8); fp32 or bf16 operands.  Used for strides and addresses that
+//     k_attn_f32 does not take.
 //   * k_attn_fa: bf16, head_dim 128, gfx950 matrix cores (v_mfma_f32_32x32x16_bf16).  Each wave owns
 //     32 queries.  Scores are formed transposed, S^T = K Q^T, so every lane holds 16 scores of one
 //     query (its partner lane l^32 holds the other 16 of a 32-key slab): the online-softmax max is a
@@ -412,6 +414,354 @@ __global__ __launch_bounds__(256, 2) void k_attn_fa(AttnP p) {
   }
 }
 
+// ------------------------------------------------------- fp32 matrix-core attention (fp32 mode, small heads)
+// softmax(q k^T / sqrt(dh)) v with every product and sum in fp32 (v_mfma_f32_32x32x2_f32), for fp32
+// operands of any head dim and bf16 ones (widened on the way into LDS) of head dims below 128.  A wave owns
+// 32 queries.  S^T = K Q^T: a lane holds 16 scores of one query, keys 8 a + 4 g + b (g = lane >> 5), its
+// partner lane ^ 32 the other 16 of the 32-key slab, so the probabilities feed O^T += V^T P^T from the
+// registers the scores came in, two keys a step (8 a + b and 8 a + 4 + b).  Row i of O's tile dt is head dim
+// DT i + dt, so that one 16-byte read of V gives a lane its operand of all four tiles.  KSP groups of waves
+// share the query block and take a 32-key slab each of every tile of 32 KSP keys; they are merged through
+// LDS at the end.  K and V tiles have one LDS buffer each, filled (fp32: by loads that write LDS
+// themselves) while the other one is worked on, two barriers a tile; two workgroups share a CU.  The
+// exponentials of tile j stand between the MFMAs of S(j + 1), the maxima of S(j + 1) between those of
+// O += V(j) P(j).  Bound by the matrix cores (157 TFLOP/s nominal): at 8 x 16 heads of 2048 x 2048 and head
+// dim 128 they are busy 81% of the cycles (115 TFLOP/s, at 2.15 GHz); 4 x 12 heads of 1560 x 512 take 189 us
+// and 12 heads of 1560 x 1560 229, where k_attn_valu takes 3207 and 4927; bf16, 4 x 16 heads of 1560 x 1560
+// and head dim 64, 410 against 2049.
+namespace af {
+constexpr int OUT_OF_RANGE = (int)0x80000000u;
+// 16-byte chunk c of row r is kept at chunk c ^ swz(r), so that the 16 lanes of a read phase, 16 rows at one
+// chunk, fall into 16 different chunks of the 256-byte bank window
+template <int DH> __device__ __forceinline__ int swz(int r) {
+  constexpr int NC = DH / 4 < 16 ? DH / 4 : 16;   // chunks of a row within the window
+  return (r / (16 / NC)) & (NC - 1);
+}
+}  // namespace af
+
+template <typename T, int DH, int KSP>
+__global__ __launch_bounds__(256, 2) void k_attn_f32(AttnP p) {
+  constexpr bool F32 = sizeof(T) == 4;
+  constexpr int QWV = 4 / KSP, QB = 32 * QWV, KT = 32 * KSP;   // query waves, queries, keys of a tile
+  constexpr int ROW = DH * 4, TILE = KT * ROW;                 // bytes
+  constexpr int DT = DH < 32 ? 1 : DH / 32, SS = DH / 8;       // output tiles, chunk pairs of a row
+  constexpr int PIECE = F32 ? 4 : 8;                           // elements of a 16-byte global load
+  constexpr int LPT = KT * DH / PIECE;                         // 16-byte loads of a tile
+  constexpr int PER = (LPT + 255) / 256;                       // per thread
+  extern __shared__ __attribute__((aligned(16))) char smf[];
+  char *sK = smf, *sV = smf + TILE;
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, li = lane & 31;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6), grp = w / QWV;
+  // XCD x (workgroups go round by id) takes a contiguous range of the (unit, query block) pairs, so that a
+  // unit's K and V stay in one or two L2s and every XCD gets its share however few units there are
+  const int total = p.batch * p.heads * p.nqb, xcd = blockIdx.x & 7;
+  const int pair = xcd * (total >> 3) + min(xcd, total & 7) + (blockIdx.x >> 3);
+  const int u = pair / p.nqb, h = u / p.batch, b = u % p.batch;
+  const int q0 = pair % p.nqb * QB + 32 * (w % QWV);
+  const bool idle = q0 >= p.tq;   // loads its share of every tile and meets every barrier, nothing else
+  const int kb = kv_batch(p, b);
+  const T *Kb = (const T *)p.k + (int64_t)kb * p.kv_bs + h * DH;
+  const T *Vb = (const T *)p.v + (int64_t)kb * p.kv_bs + h * DH;
+  const int nt = (p.tk + KT - 1) / KT;
+
+  float q[SS][4];
+  {
+    const T *Q = (const T *)p.q + (int64_t)b * p.q_bs + (int64_t)min(q0 + li, p.tq - 1) * p.q_rs + h * DH;
+#pragma unroll
+    for (int s = 0; s < SS; ++s)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) q[s][i] = to_f32(Q[8 * s + 4 * g + i]) * p.qscale;
+  }
+
+  // tile j of K or V into its LDS buffer: issue() starts the loads, land() makes them LDS contents (to be
+  // followed by a barrier).  Keys at or past tk are zero.
+  u32x4 held[F32 ? 1 : PER];
+  auto issue = [&](const T *base, char *dst, int j, bool swizzled) {
+    const T *tile = base + (int64_t)j * KT * p.kv_rs;
+    const int valid = min(KT, p.tk - j * KT);
+    if constexpr (F32) {
+      const uint64_t a = (uint64_t)tile;
+      const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a), hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
+      const uint32_t bytes = __builtin_amdgcn_readfirstlane((uint32_t)((valid - 1) * (int)p.kv_rs + DH) * 4u);
+      const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void *)(((uint64_t)hi << 32) | lo), (short)0, (int)bytes, 0x00020000);
+#pragma unroll
+      for (int x = 0; x < PER; ++x) {
+        const int i = 4 * x + w;              // load instruction: 64 chunks of the tile
+        if (64 * i >= LPT) break;
+        const int c = 64 * i + lane, row = c / (DH / 4), cc = (c % (DH / 4)) ^ (swizzled ? af::swz<DH>(row) : 0);
+        const int off = row < valid ? (row * (int)p.kv_rs + 4 * cc) * 4 : af::OUT_OF_RANGE;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void *)(dst + 1024 * i), 16, off, 0, 0, 0);
+      }
+    } else {
+#pragma unroll
+      for (int x = 0; x < PER; ++x) {
+        const int c = 256 * x + tid, row = c / (DH / 8), c8 = c % (DH / 8);
+        held[x] = u32x4{0, 0, 0, 0};
+        if (c < LPT && row < valid) held[x] = *reinterpret_cast<const u32x4 *>(tile + (int64_t)row * p.kv_rs + 8 * c8);
+      }
+    }
+  };
+  auto land = [&](char *dst, bool swizzled) {
+    if constexpr (F32) {
+      __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+    } else {
+#pragma unroll
+      for (int x = 0; x < PER; ++x) {
+        const int c = 256 * x + tid, row = c / (DH / 8), c8 = c % (DH / 8), sw = swizzled ? af::swz<DH>(row) : 0;
+        if (c >= LPT) break;
+        const bf16x8 v = __builtin_bit_cast(bf16x8, held[x]);
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf)
+          *reinterpret_cast<f32x4 *>(dst + row * ROW + (((2 * c8 + hf) ^ sw) << 4)) =
+              f32x4{(float)v[4 * hf], (float)v[4 * hf + 1], (float)v[4 * hf + 2], (float)v[4 * hf + 3]};
+      }
+    }
+  };
+
+  f32x16 o[DT];
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) o[dt][i] = 0.f;
+  float mrun = -INFINITY, lsum = 0.f;   // lsum: this lane's keys only
+
+  const int krow = 32 * grp + li;
+  const int vdim = min(DT * li, DH - DT);   // head dims below 32: the tile's rows past them repeat the last
+  auto kfrag = [&](int s) __attribute__((always_inline)) {
+    return *reinterpret_cast<const f32x4 *>(sK + krow * ROW + (((2 * s + g) ^ af::swz<DH>(krow)) << 4));
+  };
+  typedef float vfrag_t __attribute__((ext_vector_type(DT)));
+  auto vfrag = [&](int i) __attribute__((always_inline)) {
+    return *reinterpret_cast<const vfrag_t *>(sV + (32 * grp + 8 * (i >> 2) + 4 * g + (i & 3)) * ROW + vdim * 4);
+  };
+  // keys at or past tk get -inf (the ragged last tile j); the maximum over both lanes of a query
+  auto mask_tail = [&](f32x16 &sc, int j) __attribute__((always_inline)) {
+    const int lim = p.tk - j * KT - 32 * grp - 4 * g;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) sc[i] = 8 * (i >> 2) + (i & 3) < lim ? sc[i] : -INFINITY;
+  };
+  auto max_pair = [&](float t) __attribute__((always_inline)) {
+    const uint32_t u = __builtin_bit_cast(uint32_t, t);
+    const auto sw = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return fmaxf(__builtin_bit_cast(float, (uint32_t)sw[0]), __builtin_bit_cast(float, (uint32_t)sw[1]));
+  };
+  // slot s of a phase of SS slots: the share of the 16 probabilities of sc that falls to it
+  float corr = 0.f, mb = 0.f;
+  auto softmax_slot = [&](f32x16 &sc, int s) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 16 * s / SS; i < 16 * (s + 1) / SS; ++i) {
+      sc[i] = exp2f(sc[i] - mb);
+      lsum += sc[i];
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) o[dt][i] *= corr;
+    }
+  };
+
+  issue(Kb, sK, 0, true);
+  land(sK, true);
+  __syncthreads();
+  f32x16 sc;
+  float tmax = -INFINITY;
+  if (!idle) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) sc[i] = 0.f;
+#pragma unroll
+    for (int s = 0; s < SS; ++s) {
+      const f32x4 kf = kfrag(s);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) sc = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[i], q[s][i], sc, 0, 0, 0);
+    }
+    if (KT > p.tk) mask_tail(sc, 0);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) tmax = fmaxf(tmax, sc[i]);
+    tmax = max_pair(tmax);
+  }
+  __syncthreads();   // nobody reads K(0) any more
+  if (nt > 1) issue(Kb, sK, 1, true);
+  if (nt > 1) land(sK, true);
+  issue(Vb, sV, 0, false);
+  if (nt > 1) __syncthreads();   // K(1) is there
+  // Step j, with S(j) and its maxima at hand, K(j + 1) in LDS and V(j) on its way: first the MFMAs of S(j + 1)
+  // with the exponentials of S(j) and the rescaling of O between them, then those of O += V(j) P(j) with the
+  // maxima of S(j + 1) after them.
+  for (int j = 0; j < nt; ++j) {
+    f32x16 sn = sc;
+    if (!idle) {
+      const float mnew = fmaxf(mrun, tmax);
+      corr = mrun == -INFINITY ? 0.f : exp2f(mrun - mnew);   // 0: nothing summed yet
+      mrun = mnew;
+      mb = mnew == -INFINITY ? 0.f : mnew;                   // a slab wholly past tk: all probabilities 0
+      lsum *= corr;
+      if (j + 1 < nt) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) sn[i] = 0.f;
+        f32x4 kf[2] = {kfrag(0), kfrag(SS > 1 ? 1 : 0)};
+#pragma unroll
+        for (int s = 0; s < SS; ++s) {
+          const f32x4 k = kf[s & 1];
+          if (s + 2 < SS) kf[s & 1] = kfrag(s + 2);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) sn = __builtin_amdgcn_mfma_f32_32x32x2f32(k[i], q[s][i], sn, 0, 0, 0);
+          softmax_slot(sc, s);
+          // the vector work between the MFMAs, not after the last of them
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one MFMA
+            __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);   // five VALU instructions
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        if ((j + 2) * KT > p.tk) mask_tail(sn, j + 1);
+      } else {
+#pragma unroll
+        for (int s = 0; s < SS; ++s) softmax_slot(sc, s);
+      }
+    }
+    land(sV, false);
+    __syncthreads();   // V(j) is there; nobody reads K(j + 1) any more
+    if (j + 2 < nt) issue(Kb, sK, j + 2, true);
+    if (!idle) {
+      vfrag_t vf[2] = {vfrag(0), vfrag(1)};
+      float t = -INFINITY;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const vfrag_t v = vf[i & 1];
+        if (i + 2 < 16) vf[i & 1] = vfrag(i + 2);
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) o[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(v[dt], sc[i], o[dt], 0, 0, 0);
+        t = fmaxf(t, sn[i]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      tmax = max_pair(t);
+      sc = sn;
+    }
+    if (j + 1 < nt) {
+      if (j + 2 < nt) land(sK, true);
+      __syncthreads();   // K(j + 2) is there; nobody reads V(j) any more
+      issue(Vb, sV, j + 1, false);
+    }
+  }
+  lsum += __shfl_xor(lsum, 32, 64);
+  if constexpr (KSP > 1) {
+    // merge the groups of each query wave: group x > 0 leaves (O, maximum, sum) in LDS, group 0 adds them up
+    constexpr int SLOT = 64 * (16 * DT + 2) * 4;   // bytes of one wave's state
+    __syncthreads();   // every wave is past its last reads of the buffers
+    auto slot = [&](int x) { return reinterpret_cast<float *>(smf + ((x - 1) * QWV + w % QWV) * SLOT) + lane; };
+    if (grp > 0) {
+      float *d = slot(grp);
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) d[64 * (16 * dt + i)] = o[dt][i];
+      d[64 * 16 * DT] = mrun;
+      d[64 * (16 * DT + 1)] = lsum;
+    }
+    __syncthreads();
+    if (grp > 0) return;
+#pragma unroll
+    for (int x = 1; x < KSP; ++x) {
+      const float *d = slot(x);
+      const float mx = d[64 * 16 * DT], lx = d[64 * (16 * DT + 1)];
+      const float mnew = fmaxf(mrun, mx);
+      const float c0 = mrun == -INFINITY ? 0.f : exp2f(mrun - mnew), c1 = mx == -INFINITY ? 0.f : exp2f(mx - mnew);
+      lsum = lsum * c0 + lx * c1;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o[dt][i] = o[dt][i] * c0 + d[64 * (16 * dt + i)] * c1;
+      mrun = mnew;
+    }
+  }
+  if (q0 + li >= p.tq) return;
+  const float inv = 1.0f / lsum;
+  T *O = (T *)p.out + (int64_t)b * p.o_bs + (int64_t)(q0 + li) * p.o_rs + h * DH;
+  // element i of tile dt: head dim DT (8 (i / 4) + 4 g + i % 4) + dt
+#pragma unroll
+  for (int a = 0; a < 4; ++a) {
+    const int d0 = DT * (8 * a + 4 * g);   // 4 DT consecutive head dims
+    if (d0 >= DH) break;
+    float v[4 * DT];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) v[DT * i + dt] = o[dt][4 * a + i] * inv;
+    if constexpr (F32) {
+#pragma unroll
+      for (int x = 0; x < DT; ++x) reinterpret_cast<f32x4 *>(O + d0)[x] = f32x4{v[4 * x], v[4 * x + 1], v[4 * x + 2], v[4 * x + 3]};
+    } else {
+#pragma unroll
+      for (int x = 0; x < DT; ++x)
+        reinterpret_cast<bf16x4 *>(O + d0)[x] = bf16x4{(bf16)v[4 * x], (bf16)v[4 * x + 1], (bf16)v[4 * x + 2], (bf16)v[4 * x + 3]};
+    }
+  }
+}
+
+template <typename T, int DH, int KSP>
+static hipError_t launch_f32_slabs(AttnP p, hipStream_t s) {
+  // the K and V tiles, later the waves' states to merge
+  constexpr size_t tiles = (size_t)2 * 32 * KSP * DH * 4;
+  constexpr size_t states = (size_t)(KSP - 1) * (4 / KSP) * 64 * (16 * (DH < 32 ? 1 : DH / 32) + 2) * 4;
+  constexpr size_t lds = tiles > states ? tiles : states;
+  auto kern = k_attn_f32<T, DH, KSP>;
+  static bool attr_set = false;
+  if (!attr_set) {
+    hipError_t err = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (err != hipSuccess) return err;
+    attr_set = true;
+  }
+  constexpr int QB = 128 / KSP;
+  p.nqb = (p.tq + QB - 1) / QB;
+  hipLaunchKernelGGL(kern, dim3((unsigned)((int64_t)p.batch * p.heads * p.nqb)), dim3(256), lds, s, p);
+  return hipGetLastError();
+}
+
+// Into how many slabs a key tile is split between the waves of a workgroup (1, 2 or 4; 128, 64 or 32 queries
+// each).  A launch takes ceil(workgroups / CUs) rounds of ceil(keys / (32 slabs)) tiles: 4.7 us a tile at head
+// dim 128 (8192 cycles of MFMA on each wave; 5.4 with four slabs), in proportion to the MFMAs below (heads
+// under 32 fill a 32-wide output tile) plus a share for the softmax.  To that come 5, 6.5 or 9 us (launch, first
+// tile, merge; 5 with four slabs below head dim 128); four slabs of head dim 128 leave one workgroup a CU's
+// LDS, which pays them in every round.  Measured (1, 2, 4 slabs): head dim 128, 12 heads of 400 x 400 64, 40,
+// 29 us; 2 x 12 heads of 1560 x 1560 415, 335, 376; 4 x 12 heads of 1560 x 512 221, 189, 277; 32 heads of
+// 1000 x 77 25, 28, 49; 2 heads of 4096 x 4096 571, 305, 182; head dim 16, 32 heads of 700 x 700 32, 29, 24.
+static int attn_slabs(const AttnP &p, int dh) {
+  // FLASHBON_ATTN_F32 (tests and tuning): "valu" or the number of slabs
+  const char *force = getenv("FLASHBON_ATTN_F32");
+  if (force && (atoi(force) == 1 || atoi(force) == 2 || atoi(force) == 4)) return atoi(force);
+  int cus = 256, dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
+    cus = 256;
+  const double mfma = (dh / 2 + 16.0 * (dh < 32 ? 1 : dh / 32)) / 128 + (dh < 128 ? 0.06 : 0.0);
+  auto cost = [&](int slabs, double tile, double fixed) {
+    const int64_t wgs = (int64_t)p.batch * p.heads * ((p.tq + 128 / slabs - 1) / (128 / slabs));
+    const double rounds = (double)((wgs + cus - 1) / cus), tiles = (p.tk + 32 * slabs - 1) / (32 * slabs);
+    return rounds * tiles * tile * mfma + fixed * (slabs == 4 && dh == 128 ? rounds : 1);
+  };
+  const double c1 = cost(1, 4.7, 5.0), c2 = cost(2, 4.7, 6.5), c4 = cost(4, 5.4, dh == 128 ? 9.0 : 5.0);
+  return c1 <= c2 && c1 <= c4 ? 1 : c2 <= c4 ? 2 : 4;
+}
+
+template <typename T, int DH>
+static hipError_t launch_f32_dh(const AttnP &p, hipStream_t s) {
+  switch (attn_slabs(p, DH)) {
+    case 4: return launch_f32_slabs<T, DH, 4>(p, s);
+    case 2: return launch_f32_slabs<T, DH, 2>(p, s);
+    default: return launch_f32_slabs<T, DH, 1>(p, s);
+  }
+}
+
+// Whether k_attn_f32 takes the call: K, V and the output in whole 16-byte pieces (bf16 outputs in 8-byte
+// ones), key rows whose offsets within a tile fit 31 bits, and a grid that does.
+template <typename T>
+static bool f32_takes(const AttnP &p) {
+  const char *force = getenv("FLASHBON_ATTN_F32");
+  if (force && !strcmp(force, "valu")) return false;
+  const int64_t piece = 16 / sizeof(T), opiece = 4;
+  return ((uintptr_t)p.k | (uintptr_t)p.v) % 16 == 0 && p.kv_bs % piece == 0 && p.kv_rs % piece == 0 && p.kv_rs >= 0 &&
+         p.kv_rs <= 1 << 21 && (uintptr_t)p.out % (opiece * sizeof(T)) == 0 && p.o_bs % opiece == 0 && p.o_rs % opiece == 0 &&
+         (int64_t)p.batch * p.heads * ((p.tq + 31) / 32) < (int64_t)1 << 31;
+}
+
 template <typename T>
 static hipError_t launch_valu(const AttnP &p, int dh, hipStream_t s) {
   dim3 grid((p.tq + 63) / 64, p.heads, p.batch), block(64);
@@ -424,6 +774,21 @@ static hipError_t launch_valu(const AttnP &p, int dh, hipStream_t s) {
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
+}
+
+template <typename T>
+static hipError_t launch_f32(const AttnP &p, int dh, hipStream_t s) {
+  if (!f32_takes<T>(p)) return launch_valu<T>(p, dh, s);
+  switch (dh) {
+    case 8: return launch_f32_dh<T, 8>(p, s);
+    case 16: return launch_f32_dh<T, 16>(p, s);
+    case 32: return launch_f32_dh<T, 32>(p, s);
+    case 64: return launch_f32_dh<T, 64>(p, s);
+    case 128:
+      if constexpr (sizeof(T) == 4) return launch_f32_dh<T, 128>(p, s);
+      return hipErrorInvalidValue;   // k_attn_fa
+    default: return hipErrorInvalidValue;
+  }
 }
 
 hipError_t launch_attention(ActType t, const AttnArgs &a, hipStream_t s) {
@@ -444,8 +809,7 @@ hipError_t launch_attention(ActType t, const AttnArgs &a, hipStream_t s) {
     hipLaunchKernelGGL(k_attn_fa, dim3((unsigned)(units8 * p.nqb)), dim3(256), 0, s, p);
     return hipGetLastError();
   }
-  if (t == ACT_BF16) return launch_valu<bf16>(p, a.head_dim, s);
-  return launch_valu<float>(p, a.head_dim, s);
+  return t == ACT_BF16 ? launch_f32<bf16>(p, a.head_dim, s) : launch_f32<float>(p, a.head_dim, s);
 }
 
 }  // namespace fb
