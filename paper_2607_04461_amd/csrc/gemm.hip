@@ -30,6 +30,37 @@
 namespace fb {
 
 // ---------------------------------------------------------------------------------- epilogues
+// The latent pixels of token row m = candidate * T + token, token = i * (W/p) + j; column
+// c p^2 + p di + dj is pixel (c, p i + di, p j + dj).
+struct EulerRow {
+  int64_t z0;   // of pixel (0, p i, p j)
+  __device__ __forceinline__ EulerRow(const EpiArgs &e, int m) {
+    const int b = m / e.T, t = m - b * e.T, wp = e.W / e.p, i = t / wp, j = t - i * wp;
+    z0 = ((int64_t)b * e.C * e.H + e.p * i) * e.W + e.p * j;
+  }
+  // pixel row di of channel c
+  __device__ __forceinline__ int64_t at(const EpiArgs &e, int c, int di) const {
+    return z0 + ((int64_t)c * e.H + di) * e.W;
+  }
+  __device__ __forceinline__ int64_t of_column(const EpiArgs &e, int n) const {
+    const int pp = e.p * e.p, c = n / pp, r = n - c * pp, di = r / e.p;
+    return at(e, c, di) + (r - di * e.p);
+  }
+};
+// z += dt v at pixel zi; the clean-latent estimate z - t v first, where it is asked for
+__device__ __forceinline__ void euler1(const EpiArgs &e, int64_t zi, float v) {
+  const float z0 = e.z[zi];
+  if (e.preview) e.preview[zi] = z0 - e.t_cur * v;
+  e.z[zi] = z0 + e.dt * v;
+}
+// two pixels side by side
+__device__ __forceinline__ void euler2(const EpiArgs &e, int64_t zi, float v0, float v1) {
+  typedef float f32x2u __attribute__((ext_vector_type(2), aligned(4)));
+  const f32x2u z0 = *reinterpret_cast<const f32x2u *>(e.z + zi);
+  if (e.preview) *reinterpret_cast<f32x2u *>(e.preview + zi) = f32x2u{z0[0] - e.t_cur * v0, z0[1] - e.t_cur * v1};
+  *reinterpret_cast<f32x2u *>(e.z + zi) = f32x2u{z0[0] + e.dt * v0, z0[1] + e.dt * v1};
+}
+
 template <int EPI, typename TO>
 __device__ __forceinline__ void epilogue4(const EpiArgs &e, int m, int n, float v0, float v1,
                                           float v2, float v3) {
@@ -73,17 +104,13 @@ __device__ __forceinline__ void epilogue4(const EpiArgs &e, int m, int n, float 
       }
     }
   } else if constexpr (EPI == EPI_EULER) {
-    // m = candidate * T + token, token = i * (W/p) + j; n = c p^2 + p di + dj
-    const int b = m / e.T, t = m % e.T, wp = e.W / e.p;
-    const int i = t / wp, j = t % wp, pp = e.p * e.p;
+    const EulerRow r(e, m);
+    if (e.p == 2) {   // four columns (n % 4 == 0) are the 2 x 2 pixels of one channel
+      euler2(e, r.at(e, n >> 2, 0), v[0], v[1]);
+      euler2(e, r.at(e, n >> 2, 1), v[2], v[3]);
+    } else {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      int nn = n + q;
-      int c = nn / pp, r = nn % pp, di = r / e.p, dj = r % e.p;
-      const int64_t zi = (((int64_t)b * e.C + c) * e.H + (e.p * i + di)) * e.W + (e.p * j + dj);
-      const float z0 = e.z[zi];
-      if (e.preview) e.preview[zi] = z0 - e.t_cur * v[q];   // clean-latent estimate z - t v
-      e.z[zi] = z0 + e.dt * v[q];
+      for (int q = 0; q < 4; ++q) euler1(e, r.of_column(e, n + q), v[q]);
     }
   }
 }
@@ -1132,6 +1159,110 @@ __global__ __launch_bounds__(256, 1) void k_linear_dma(int M, int N, int K, cons
   }
   dma_tile<EPI, TO, WTA>(M, N, K, A, Wt, e, m0, n0, smem);
 }
+// -------------------------------------------------------------------------- few output columns
+// The head of the network with the latent update: bf16 operands, 32 rows x 64 columns per workgroup (all of
+// a head's columns at C p^2 = 64), one pass over A.  The waves take the K chunks of 64 in turn, their
+// fragments straight from memory (a lane's 16 bytes of A and W rows are the MFMA operands), one chunk ahead;
+// the sums are added through LDS in wave order, and the tile is then walked along the latent's rows, whose
+// pixels were read at the start.  Four waves, three workgroups a CU; eight where the tiles leave CUs idle.
+// Bound by A's rows at many tokens and by the chain of loads at few: K = 1536 with 24960 rows 44 us, K = 256
+// with 390 rows 5.4 us.  The 128x128 and 256x256 tiles of the other layers, with four divisions an
+// output in their epilogue, took 58 and 53 us; with the pixels read after the sums this kernel took 50 and 7.
+namespace nar {
+constexpr int BM = 32, BN = 64, LDR = BN + 4;   // LDR: floats of a row of sums
+}
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 2 : 3) void k_linear_head(int M, int N, int K, const bf16 *__restrict__ A,
+                                                               const bf16 *__restrict__ Wt, EpiArgs e) {
+  using namespace nar;
+  __shared__ __attribute__((aligned(16))) float sums[WAVES][BM][LDR];
+  const int tid = threadIdx.x, lane = tid & 63, fr = lane & 15, fq = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int m0 = blockIdx.x * BM, n0 = blockIdx.y * BN;
+  // rows past the end and columns past K read as zero
+  const __amdgpu_buffer_rsrc_t rsA = epi::rsrc(A + (int64_t)m0 * K, (uint32_t)min(M - m0, BM) * (uint32_t)K * 2u);
+  const __amdgpu_buffer_rsrc_t rsW = epi::rsrc(Wt + (int64_t)n0 * K, (uint32_t)min(N - n0, BN) * (uint32_t)K * 2u);
+  const int chunks = (K + 63) / 64;
+  u32x4 fa[2][2][2], fw[2][4][2];   // [buffer][16 rows][32 columns of K]
+  auto load = [&](int ch, int buf) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int k = 64 * ch + 32 * h + 8 * fq;
+      const uint32_t kb = k < K ? (uint32_t)k * 2u : epi::OUT_OF_RANGE;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) fa[buf][j][h] = __builtin_amdgcn_raw_buffer_load_b128(rsA, (uint32_t)((16 * j + fr) * K) * 2u + kb, 0, 0);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) fw[buf][i][h] = __builtin_amdgcn_raw_buffer_load_b128(rsW, (uint32_t)((16 * i + fr) * K) * 2u + kb, 0, 0);
+    }
+  };
+  f32x4 acc[4][2];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0, 0, 0, 0};
+  auto mul = [&](int buf) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fw[buf][i][h]),
+                                                              __builtin_bit_cast(bf16x8, fa[buf][j][h]), acc[i][j], 0, 0, 0);
+  };
+  // p = 2, lanes 2 x, 2 x + 1: the two pixels of a pixel row of token x; a wave takes the pixel rows in turn.
+  // The latents are read now, so that their latency passes under the sums.
+  constexpr int NZ = BN / 2 / WAVES;
+  const int tok = m0 + (lane >> 1), dj = lane & 1;
+  const bool pairs = e.p == 2;
+  float z[NZ];
+  int64_t zi[NZ];
+  if (pairs && tok < M) {
+    const EulerRow r(e, tok);
+#pragma unroll
+    for (int x = 0; x < NZ; ++x) {
+      const int cd = wave + WAVES * x;
+      zi[x] = r.at(e, (n0 >> 2) + (cd >> 1), cd & 1) + dj;
+      if (n0 + 2 * cd < N) z[x] = e.z[zi[x]];
+    }
+  }
+  if (wave < chunks) load(wave, 0);
+  for (int ch = wave; ch < chunks; ch += 2 * WAVES) {
+    if (ch + WAVES < chunks) load(ch + WAVES, 1);
+    mul(0);
+    if (ch + 2 * WAVES < chunks) load(ch + 2 * WAVES, 0);
+    if (ch + WAVES < chunks) mul(1);
+  }
+  // acc[i][j]: columns 16 i + 4 fq .. + 3 of row 16 j + fr
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) *reinterpret_cast<f32x4 *>(&sums[wave][16 * j + fr][16 * i + 4 * fq]) = acc[i][j];
+  __syncthreads();
+  const int used = min(WAVES, chunks);
+  auto value = [&](int row, int col) {
+    float v = sums[0][row][col];
+    for (int w = 1; w < used; ++w) v += sums[w][row][col];
+    return e.bias ? v + e.bias[n0 + col] : v;
+  };
+  if (pairs) {
+    if (tok >= M) return;
+#pragma unroll
+    for (int x = 0; x < NZ; ++x) {
+      const int cd = wave + WAVES * x;
+      if (n0 + 2 * cd >= N) break;
+      const float v = value(lane >> 1, 2 * cd + dj);
+      if (e.preview) e.preview[zi[x]] = z[x] - e.t_cur * v;
+      e.z[zi[x]] = z[x] + e.dt * v;
+    }
+  } else {
+    for (int x = tid; x < BM * BN; x += 64 * WAVES) {
+      const int row = x / BN, col = x % BN;
+      if (m0 + row < M && n0 + col < N) euler1(e, EulerRow(e, m0 + row).of_column(e, n0 + col), value(row, col));
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------------- fp32 path
 // fp32 operands on the matrix cores (v_mfma_f32_32x32x2_f32: 256 FLOP per cycle and CU, twice what the
 // vector ALUs give).  Workgroup tiles of (32 TM WGM) x (32 TN WGN); K tiles of 32 floats, so that an LDS
@@ -1623,15 +1754,12 @@ static EpiArgs rows_from(const EpiArgs &e, int m) {
 }
 
 // 256x256 tiles: the 8-wave kernel with LDS-writing loads when it takes the shape, else the generic
-// 8-wave kernel with register-staged loads (K % 64 != 0, K < 128 or N % 8 != 0, and the latent
-// scatter).
+// 8-wave kernel with register-staged loads (K % 64 != 0, K < 128 or N % 8 != 0).
 template <int EPI>
 static hipError_t launch_big(int M, int N, int K, const void *A, const void *Wt, const EpiArgs &e, hipStream_t s) {
-  if constexpr (EPI != EPI_EULER) {
-    if (K % mf::BK == 0 && K >= 2 * mf::BK && N % 8 == 0) {
-      const int mb = (M + 255) / 256;
-      return launch_dma8<EPI, 8>(M, N, K, A, Wt, e, s, mb, mb);
-    }
+  if (K % mf::BK == 0 && K >= 2 * mf::BK && N % 8 == 0) {
+    const int mb = (M + 255) / 256;
+    return launch_dma8<EPI, 8>(M, N, K, A, Wt, e, s, mb, mb);
   }
   return launch_mfma<8, 4, 2, 4, EPI, 1>(M, N, K, A, Wt, e, s);
 }
@@ -1682,45 +1810,56 @@ static hipError_t launch_f32(int M, int N, int K, const float *A, const float *W
   return hipGetLastError();
 }
 
+// bf16 operands, every epilogue but the latent scatter.
+template <int EPI>
+static hipError_t launch_bf16(int M, int N, int K, const void *A, const void *Wt, const EpiArgs &e, hipStream_t s) {
+  const bool dma_ok = K % mf::BK == 0 && K >= 2 * mf::BK && N % 8 == 0;
+  const TileChoice c = pick_tiles(M, N, K, dma_ok);
+  if (c.plan == PLAN_SMALL) return launch_mfma<4, 4, 2, 2, EPI, 2>(M, N, K, A, Wt, e, s);
+  if (c.plan == PLAN_BIG) return launch_big<EPI>(M, N, K, A, Wt, e, s);
+  if (c.plan == PLAN_DEEP) {
+    const int key = 100 * c.wta + 10 * c.wt + c.nst;
+    switch (key) {
+      case 422: return launch_deep<EPI, 4, 2, 2>(M, N, K, A, Wt, e, s);
+      case 423: return launch_deep<EPI, 4, 2, 3>(M, N, K, A, Wt, e, s);
+      case 522: return launch_deep<EPI, 5, 2, 2>(M, N, K, A, Wt, e, s);
+      case 523: return launch_deep<EPI, 5, 2, 3>(M, N, K, A, Wt, e, s);
+      case 442: return launch_deep<EPI, 4, 4, 2>(M, N, K, A, Wt, e, s);
+      case 443: return launch_deep<EPI, 4, 4, 3>(M, N, K, A, Wt, e, s);
+      case 542: return launch_deep<EPI, 5, 4, 2>(M, N, K, A, Wt, e, s);
+      case 543: return launch_deep<EPI, 5, 4, 3>(M, N, K, A, Wt, e, s);
+      default: return hipErrorInvalidValue;
+    }
+  }
+  if (c.plan == PLAN_MIX && c.waves == 8) {
+    if (c.wta == 8) return launch_dma8<EPI, 8>(M, N, K, A, Wt, e, s, c.mb, c.tall);
+    if (c.wta == 7) return launch_dma8<EPI, 7>(M, N, K, A, Wt, e, s, c.mb, c.tall);
+    return launch_dma8<EPI, 6>(M, N, K, A, Wt, e, s, c.mb, c.tall);
+  }
+  if (c.plan == PLAN_MIX) {
+    if (c.wta == 8) return launch_dma<EPI, 8>(M, N, K, A, Wt, e, s, c.mb, c.tall);
+    if (c.wta == 7) return launch_dma<EPI, 7>(M, N, K, A, Wt, e, s, c.mb, c.tall);
+    return launch_dma<EPI, 6>(M, N, K, A, Wt, e, s, c.mb, c.tall);
+  }
+  hipError_t err = launch_big<EPI>(c.rows, N, K, A, Wt, e, s);
+  if (err != hipSuccess) return err;
+  return launch_mfma<4, 4, 2, 2, EPI, 2>(M - c.rows, N, K, (const bf16 *)A + (size_t)c.rows * K, Wt,
+                                         rows_from<EPI>(e, c.rows), s);
+}
+
 template <int EPI>
 static hipError_t launch_epi(ActType t, int M, int N, int K, const void *A, const void *Wt,
                              const EpiArgs &e, hipStream_t s) {
   if (t == ACT_BF16) {
-    const bool dma_ok = EPI != EPI_EULER && K % mf::BK == 0 && K >= 2 * mf::BK && N % 8 == 0;
-    TileChoice c = pick_tiles(M, N, K, dma_ok);
-    if (c.plan == PLAN_SPLIT && EPI == EPI_EULER) c = {PLAN_BIG, 8, 0, 0, 0};   // the latent scatter needs whole rows
-    if (c.plan == PLAN_SMALL) return launch_mfma<4, 4, 2, 2, EPI, 2>(M, N, K, A, Wt, e, s);
-    if (c.plan == PLAN_BIG) return launch_big<EPI>(M, N, K, A, Wt, e, s);
-    if constexpr (EPI != EPI_EULER) {
-      if (c.plan == PLAN_DEEP) {
-        const int key = 100 * c.wta + 10 * c.wt + c.nst;
-        switch (key) {
-          case 422: return launch_deep<EPI, 4, 2, 2>(M, N, K, A, Wt, e, s);
-          case 423: return launch_deep<EPI, 4, 2, 3>(M, N, K, A, Wt, e, s);
-          case 522: return launch_deep<EPI, 5, 2, 2>(M, N, K, A, Wt, e, s);
-          case 523: return launch_deep<EPI, 5, 2, 3>(M, N, K, A, Wt, e, s);
-          case 442: return launch_deep<EPI, 4, 4, 2>(M, N, K, A, Wt, e, s);
-          case 443: return launch_deep<EPI, 4, 4, 3>(M, N, K, A, Wt, e, s);
-          case 542: return launch_deep<EPI, 5, 4, 2>(M, N, K, A, Wt, e, s);
-          case 543: return launch_deep<EPI, 5, 4, 3>(M, N, K, A, Wt, e, s);
-          default: return hipErrorInvalidValue;
-        }
-      }
-      if (c.plan == PLAN_MIX && c.waves == 8) {
-        if (c.wta == 8) return launch_dma8<EPI, 8>(M, N, K, A, Wt, e, s, c.mb, c.tall);
-        if (c.wta == 7) return launch_dma8<EPI, 7>(M, N, K, A, Wt, e, s, c.mb, c.tall);
-        return launch_dma8<EPI, 6>(M, N, K, A, Wt, e, s, c.mb, c.tall);
-      }
-      if (c.plan == PLAN_MIX) {
-        if (c.wta == 8) return launch_dma<EPI, 8>(M, N, K, A, Wt, e, s, c.mb, c.tall);
-        if (c.wta == 7) return launch_dma<EPI, 7>(M, N, K, A, Wt, e, s, c.mb, c.tall);
-        return launch_dma<EPI, 6>(M, N, K, A, Wt, e, s, c.mb, c.tall);
-      }
+    if constexpr (EPI == EPI_EULER) {
+      const dim3 grid((M + nar::BM - 1) / nar::BM, (N + nar::BN - 1) / nar::BN);
+      const bool wide = (int64_t)grid.x * grid.y <= cu_count();
+      hipLaunchKernelGGL(wide ? k_linear_head<8> : k_linear_head<4>, grid, dim3(wide ? 512 : 256), 0, s, M, N, K,
+                         (const bf16 *)A, (const bf16 *)Wt, e);
+      return hipGetLastError();
+    } else {
+      return launch_bf16<EPI>(M, N, K, A, Wt, e, s);
     }
-    hipError_t err = launch_big<EPI>(c.rows, N, K, A, Wt, e, s);
-    if (err != hipSuccess) return err;
-    return launch_mfma<4, 4, 2, 2, EPI, 2>(M - c.rows, N, K, (const bf16 *)A + (size_t)c.rows * K, Wt,
-                                           rows_from<EPI>(e, c.rows), s);
   }
   const float *Af = (const float *)A, *Wf = (const float *)Wt;
   const uintptr_t at = (uintptr_t)A | (uintptr_t)Wt | (uintptr_t)e.out | (uintptr_t)e.bias | (uintptr_t)e.gate |
@@ -1742,7 +1881,9 @@ int describe_linear(ActType t, int epi, int M, int N, int K, char *buf, int len)
   std::string d;
   int kernels = 1;
   auto rows_of = [](int w) { return std::to_string(32 * w); };
-  if (t != ACT_BF16) {
+  if (t == ACT_BF16 && epi == EPI_EULER) {
+    d = "k_linear_head: 32x64 tiles, K over 8 waves";
+  } else if (t != ACT_BF16) {
     switch (f32_tile(M, N, K, true)) {   // operands on 16 bytes
       case F32_MID: d = "k_linear_f32: 64x64 tiles, fp32 matrix cores"; break;
       case F32_SMALL: d = "k_linear_f32: 32x32 tiles, K over 4 waves, fp32 matrix cores"; break;
@@ -1750,9 +1891,8 @@ int describe_linear(ActType t, int epi, int M, int N, int K, char *buf, int len)
       case F32_VALU: d = "k_linear_valu: 64x64 tiles, fp32 vector ALUs"; break;
     }
   } else {
-    const bool dma_ok = epi != EPI_EULER && K % mf::BK == 0 && K >= 2 * mf::BK && N % 8 == 0;
-    TileChoice c = pick_tiles(M, N, K, dma_ok);
-    if (c.plan == PLAN_SPLIT && epi == EPI_EULER) c = {PLAN_BIG, 8, 0, 0, 0};
+    const bool dma_ok = K % mf::BK == 0 && K >= 2 * mf::BK && N % 8 == 0;
+    const TileChoice c = pick_tiles(M, N, K, dma_ok);
     const std::string nt = std::to_string((N + 255) / 256);
     if (c.plan == PLAN_DEEP) {
       d = "k_linear_deep (8 waves): " + rows_of(c.wta) + "x" + std::to_string(64 * c.wt) + " tiles, " +
