@@ -260,154 +260,196 @@ template <> __device__ __forceinline__ void store8<bf16>(bf16 *p, const float v[
 }
 
 // In place on rows of x (stride rs): x <- RMSNorm(x) * gain over D, then, with a table, every pair
-// (2k, 2k+1) of each head rotated by the table entry of (row % T, k).  One wave per row, two passes
-// over the row (statistics, then normalise + rotate), 8 elements per lane per load.
-template <typename T>
-__global__ __launch_bounds__(256) void k_qk_norm(int M, int D, int dh, T *__restrict__ x, int64_t rs,
-                                                 const float *__restrict__ gain, float eps,
+// (2k, 2k+1) of each head rotated by the table entry of (row % tokens, k).  One wave per row, which stays in
+// registers between the statistics and the rotation (8 NV elements a lane, D <= 512 NV); blockIdx.y 1 takes
+// the second row set (x1, gain1) of the launch: the k rows beside the q rows.  Bound by the rows'
+// bytes: the two launches of a block of 3120 tokens at D = 1536 (q and k, cross-attention's q) take 16 us, where
+// three launches that read their rows twice took 22.
+template <typename T, int NV>
+__global__ __launch_bounds__(256) void k_qk_norm(int M, int D, int dh, T *__restrict__ x0, T *__restrict__ x1, int64_t rs,
+                                                 const float *__restrict__ gain0, const float *__restrict__ gain1, float eps,
                                                  const float2 *__restrict__ tab, int tokens) {
   const int lane = threadIdx.x & 63;
   const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= M) return;
-  T *xr = x + row * rs;
+  T *xr = (blockIdx.y ? x1 : x0) + row * rs;
+  const float *gain = blockIdx.y ? gain1 : gain0;
   const int chunks = D >> 3;
+  float v[NV][8];
   float ss = 0.f;
-  for (int c = lane; c < chunks; c += 64) {
-    float v[8];
-    load8<T>(xr + 8 * c, v);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) ss = fmaf(v[i], v[i], ss);
+  for (int i = 0; i < NV; ++i) {
+    const int c = lane + 64 * i;
+    if (c < chunks) {
+      load8<T>(xr + 8 * c, v[i]);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) ss = fmaf(v[i][q], v[i][q], ss);
+    }
   }
   const float rstd = 1.0f / sqrtf(wave_sum(ss) / (float)D + eps);
   const float2 *tr = tab ? tab + (row % tokens) * (dh >> 1) : nullptr;
-  for (int c = lane; c < chunks; c += 64) {
-    float v[8];
-    load8<T>(xr + 8 * c, v);
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const int c = lane + 64 * i;
+    if (c >= chunks) break;
     const float4 g0 = reinterpret_cast<const float4 *>(gain + 8 * c)[0];
     const float4 g1 = reinterpret_cast<const float4 *>(gain + 8 * c)[1];
     const float g[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
 #pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = v[i] * rstd * g[i];
-    if (tr) {
+    for (int q = 0; q < 8; ++q) v[i][q] = v[i][q] * rstd * g[q];
+    if (tr) {   // dh % 8 == 0: a chunk lies in one head
+      const float4 *cs = reinterpret_cast<const float4 *>(tr + ((8 * c) % dh >> 1));
 #pragma unroll
-      for (int pr = 0; pr < 4; ++pr) {
-        const int d = (8 * c + 2 * pr) % dh;
-        const float2 cs = tr[d >> 1];
-        const float a = v[2 * pr], b = v[2 * pr + 1];
-        v[2 * pr] = a * cs.x - b * cs.y;
-        v[2 * pr + 1] = a * cs.y + b * cs.x;
+      for (int h = 0; h < 2; ++h) {
+        const float4 t = cs[h];   // (cos, sin) of two pairs
+        const float a = v[i][4 * h], b = v[i][4 * h + 1], d = v[i][4 * h + 2], e = v[i][4 * h + 3];
+        v[i][4 * h] = a * t.x - b * t.y;
+        v[i][4 * h + 1] = a * t.y + b * t.x;
+        v[i][4 * h + 2] = d * t.z - e * t.w;
+        v[i][4 * h + 3] = d * t.w + e * t.z;
       }
     }
-    store8<T>(xr + 8 * c, v);
+    store8<T>(xr + 8 * c, v[i]);
   }
 }
 
-hipError_t launch_qk_norm(ActType t, int M, int D, int dh, void *x, int64_t rs, const float *gain, float eps,
-                          const float2 *tab, int tokens, hipStream_t s) {
-  dim3 g((unsigned)((M + 3) / 4)), b(256);
-  if (t == ACT_BF16)
-    hipLaunchKernelGGL(k_qk_norm<bf16>, g, b, 0, s, M, D, dh, (bf16 *)x, rs, gain, eps, tab, tokens);
-  else
-    hipLaunchKernelGGL(k_qk_norm<float>, g, b, 0, s, M, D, dh, (float *)x, rs, gain, eps, tab, tokens);
+template <typename T>
+static void qk_norm_t(int M, int D, int dh, T *x0, T *x1, int64_t rs, const float *gain0, const float *gain1, float eps,
+                      const float2 *tab, int tokens, hipStream_t s) {
+  const dim3 g((unsigned)((M + 3) / 4), x1 ? 2 : 1), b(256);
+#define FB_QK(NV) hipLaunchKernelGGL((k_qk_norm<T, NV>), g, b, 0, s, M, D, dh, x0, x1, rs, gain0, gain1, eps, tab, tokens)
+  if (D <= 512) FB_QK(1);
+  else if (D <= 1536) FB_QK(3);
+  else if (D <= 3072) FB_QK(6);
+  else FB_QK(12);
+#undef FB_QK
+}
+
+hipError_t launch_qk_norm(ActType t, int M, int D, int dh, void *x0, void *x1, int64_t rs, const float *gain0,
+                          const float *gain1, float eps, const float2 *tab, int tokens, hipStream_t s) {
+  if (t == ACT_BF16) qk_norm_t<bf16>(M, D, dh, (bf16 *)x0, (bf16 *)x1, rs, gain0, gain1, eps, tab, tokens, s);
+  else qk_norm_t<float>(M, D, dh, (float *)x0, (float *)x1, rs, gain0, gain1, eps, tab, tokens, s);
   return hipGetLastError();
 }
 
 // --------------------------------------------------------------------------------- timestep path
-__global__ void k_time_features(double t, int half, float *f) {
-  int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= half) return;
-  double w = pow(10000.0, -(double)j / (double)half);
-  double a = 1000.0 * t * w;
-  f[j] = (float)cos(a);
-  f[half + j] = (float)sin(a);
-}
+// The timestep path is three dependent matrix-vector products and runs once a step before anything else
+// can: three launches, each bound by its latency (9.5 MB of weights at D = 1536 in the second, 75 MB in the
+// third, which reads them at 4.2 TB/s).  It takes 28 us of a D = 1536 step and 10.5 us of a D = 256 one; as
+// six launches -- features, each product and the block tables on their own -- it took 44 and 16.
 
-hipError_t launch_time_features(double t, int freq_dim, float *f, hipStream_t s) {
-  int half = freq_dim / 2;
-  hipLaunchKernelGGL(k_time_features, dim3((half + 255) / 256), dim3(256), 0, s, t, half, f);
-  return hipGetLastError();
-}
-
-// One wave per output row; lanes stride over the row with float4 loads.
-__global__ __launch_bounds__(256) void k_gemv(int out, int in, const float *__restrict__ W,
-                                              const float *__restrict__ b,
-                                              const float *__restrict__ x, float *__restrict__ y,
-                                              int act_in, int act_out) {
-  const int lane = threadIdx.x & 63;
-  const int o = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (o >= out) return;
-  const float *wr = W + (int64_t)o * in;
+// e1 = SiLU(W f + b) with the sinusoidal features f[j] = cos(a), f[half + j] = sin(a), a = 1000 t 10000^(-j/half)
+// (computed in double by every workgroup, kFeat at a time); one wave per output row.
+constexpr int kFeat = 512;
+__global__ __launch_bounds__(256) void k_time_mlp1(double t, int half, int out, const float *__restrict__ W,
+                                                   const float *__restrict__ b, float *__restrict__ y) {
+  __shared__ float fc[kFeat], fs[kFeat];
+  const int lane = threadIdx.x & 63, o = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const float *wr = W + (int64_t)min(o, out - 1) * 2 * half;
   float acc = 0.f;
-  for (int k = lane; k < in; k += 64) {
-    float xv = x[k];
-    if (act_in == 1) xv = silu(xv);
-    acc += wr[k] * xv;
+  for (int j0 = 0; j0 < half; j0 += kFeat) {
+    const int n = min(kFeat, half - j0);
+    if (j0) __syncthreads();
+    for (int j = threadIdx.x; j < n; j += 256) {
+      const double w = pow(10000.0, -(double)(j0 + j) / (double)half), a = 1000.0 * t * w;
+      fc[j] = (float)cos(a);
+      fs[j] = (float)sin(a);
+    }
+    __syncthreads();
+    for (int j = lane; j < n; j += 64) acc += wr[j0 + j] * fc[j] + wr[half + j0 + j] * fs[j];
   }
   acc = wave_sum(acc);
-  if (lane == 0) {
-    float r = acc + (b ? b[o] : 0.f);
-    if (act_out == 1) r = silu(r);
-    y[o] = r;
-  }
+  if (lane == 0 && o < out) y[o] = silu(acc + b[o]);
 }
 
-// The same with 16-byte loads (in % 4 == 0, 16-byte aligned rows): each lane keeps four row chunks
-// in flight, so a wave streams its row at the memory rate rather than one dependent 4-byte load at a
-// time (the 6D x D modulation matrix, 56.6 MB in fp32 at D = 1536, is read once per step).
-__global__ __launch_bounds__(256) void k_gemv4(int out, int in, const float *__restrict__ W,
-                                               const float *__restrict__ b,
-                                               const float *__restrict__ x, float *__restrict__ y,
-                                               int act_in, int act_out) {
-  const int lane = threadIdx.x & 63;
-  const int o = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (o >= out) return;
-  const float4 *wr = reinterpret_cast<const float4 *>(W + (int64_t)o * in);
-  const float4 *xr = reinterpret_cast<const float4 *>(x);
-  const int n4 = in >> 2;
-  float acc[4] = {0.f, 0.f, 0.f, 0.f};
-  for (int k0 = lane; k0 < n4; k0 += 256) {
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int k = k0 + 64 * u;
-      if (k < n4) {
-        const float4 w = wr[k];
-        float4 xv = xr[k];
-        if (act_in == 1) xv = make_float4(silu(xv.x), silu(xv.y), silu(xv.z), silu(xv.w));
-        acc[u] += (w.x * xv.x + w.y * xv.y) + (w.z * xv.z + w.w * xv.w);
-      }
-    }
-  }
-  float a = wave_sum((acc[0] + acc[1]) + (acc[2] + acc[3]));
-  if (lane == 0) {
-    float r = a + (b ? b[o] : 0.f);
-    if (act_out == 1) r = silu(r);
-    y[o] = r;
-  }
-}
-
-hipError_t launch_gemv(int out, int in, const float *W, const float *b, const float *x, float *y,
-                       int act_in, int act_out, hipStream_t s) {
-  if (in % 4 == 0 && (((uintptr_t)W | (uintptr_t)x) & 15) == 0)
-    hipLaunchKernelGGL(k_gemv4, dim3((out + 3) / 4), dim3(256), 0, s, out, in, W, b, x, y, act_in, act_out);
-  else
-    hipLaunchKernelGGL(k_gemv, dim3((out + 3) / 4), dim3(256), 0, s, out, in, W, b, x, y, act_in,
-                       act_out);
+hipError_t launch_time_mlp1(double t, int freq_dim, int out, const float *W, const float *b, float *y, hipStream_t s) {
+  hipLaunchKernelGGL(k_time_mlp1, dim3((out + 3) / 4), dim3(256), 0, s, t, freq_dim / 2, out, W, b, y);
   return hipGetLastError();
 }
 
-__global__ void k_block_mods(int L, int width, const float *__restrict__ m,
-                             const float *__restrict__ tables, int64_t stride,
-                             float *__restrict__ mods) {
-  int j = blockIdx.x * blockDim.x + threadIdx.x;
-  int l = blockIdx.y;
-  if (j >= width) return;
-  mods[(int64_t)l * width + j] = m[j] + tables[l * stride + j];
+// acc[r] = row r . x for R consecutive rows of one wave (every lane ends with all R): 16-byte loads, U chunks
+// of each row in flight per lane, so that a wave streams its rows at the memory rate; SILU: x goes through
+// SiLU first.  in % 4 == 0, 16-byte aligned.
+template <bool SILU, int R, int U>
+__device__ __forceinline__ void wave_dots(const float *__restrict__ rows, const float *__restrict__ x, int in, int lane,
+                                          float (&acc)[R]) {
+  const float4 *xr = reinterpret_cast<const float4 *>(x), *wr = reinterpret_cast<const float4 *>(rows);
+  const int n4 = in >> 2;
+  float part[R][U] = {};
+  for (int k0 = lane; k0 < n4; k0 += 64 * U) {
+    float4 w[R][U], xv[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = k0 + 64 * u;
+      if (k < n4) {
+        xv[u] = xr[k];
+#pragma unroll
+        for (int r = 0; r < R; ++r) w[r][u] = wr[(int64_t)r * n4 + k];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (k0 + 64 * u >= n4) break;
+      if constexpr (SILU) xv[u] = make_float4(silu(xv[u].x), silu(xv[u].y), silu(xv[u].z), silu(xv[u].w));
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        part[r][u] += (w[r][u].x * xv[u].x + w[r][u].y * xv[u].y) + (w[r][u].z * xv[u].z + w[r][u].w * xv[u].w);
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    acc[r] = part[r][0];
+#pragma unroll
+    for (int u = 1; u < U; ++u) acc[r] += part[r][u];
+    acc[r] = wave_sum(acc[r]);
+  }
 }
 
-hipError_t launch_block_mods(int L, int width, const float *m, const float *tables,
-                             int64_t table_stride, float *mods, hipStream_t s) {
-  hipLaunchKernelGGL(k_block_mods, dim3((width + 255) / 256, L), dim3(256), 0, s, L, width, m,
-                     tables, table_stride, mods);
+__global__ __launch_bounds__(256) void k_time_mlp2(int D, const float *__restrict__ W, const float *__restrict__ b,
+                                                   const float *__restrict__ x, float *__restrict__ y) {
+  const int lane = threadIdx.x & 63, o = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (o >= D) return;
+  float a[1];
+  wave_dots<false, 1, 4>(W + (int64_t)o * D, x, D, lane, a);
+  if (lane == 0) y[o] = a[0] + b[o];
+}
+
+hipError_t launch_time_mlp2(int D, const float *W, const float *b, const float *x, float *y, hipStream_t s) {
+  hipLaunchKernelGGL(k_time_mlp2, dim3((D + 3) / 4), dim3(256), 0, s, D, W, b, x, y);
+  return hipGetLastError();
+}
+
+// The modulations of every block, mods[l] = Wm SiLU(e) + bm + table_l (6D values each), and the head's,
+// hmod = Wh SiLU(e) + bh (2D values).  A workgroup takes 16 rows of the two matrices, four a wave, and writes
+// 16 consecutive values of every block (D % 8 == 0: a workgroup's rows lie in one matrix).
+__global__ __launch_bounds__(256) void k_modulations(int L, int D, const float *__restrict__ Wm, const float *__restrict__ bm,
+                                                     const float *__restrict__ Wh, const float *__restrict__ bh,
+                                                     const float *__restrict__ e, const float *__restrict__ tables,
+                                                     int64_t stride, float *__restrict__ mods, float *__restrict__ hmod) {
+  __shared__ float m[16];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int o0 = blockIdx.x * 16, width = 6 * D;
+  const bool head = o0 >= width;
+  const float *W = head ? Wh : Wm, *b = head ? bh : bm;
+  const int row0 = head ? o0 - width : o0;
+  float a[4];
+  wave_dots<true, 4, 3>(W + (int64_t)(row0 + 4 * wave) * D, e, D, lane, a);
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+    if (lane == r) m[4 * wave + r] = a[r] + b[row0 + 4 * wave + r];
+  __syncthreads();
+  const int i = threadIdx.x & 15;
+  if (head) {
+    if (threadIdx.x < 16) hmod[row0 + i] = m[i];
+  } else {
+    for (int l = threadIdx.x >> 4; l < L; l += 16) mods[(int64_t)l * width + o0 + i] = m[i] + tables[l * stride + o0 + i];
+  }
+}
+
+hipError_t launch_modulations(int L, int D, const float *Wm, const float *bm, const float *Wh, const float *bh,
+                              const float *e, const float *tables, int64_t table_stride, float *mods, float *hmod,
+                              hipStream_t s) {
+  hipLaunchKernelGGL(k_modulations, dim3(D / 2), dim3(256), 0, s, L, D, Wm, bm, Wh, bh, e, tables, table_stride, mods, hmod);
   return hipGetLastError();
 }
 

@@ -69,16 +69,15 @@ hipError_t launch_proxy(int64_t count, const float *h1, const float *h2, const f
 hipError_t launch_patchify(ActType t, int n, int zrows, int C, int H, int W, int p, const float *z, void *tok,
                            hipStream_t s);
 
-// sinusoidal features of 1000 t, computed in double: f[j] = cos, f[half + j] = sin
-hipError_t launch_time_features(double t, int freq_dim, float *f, hipStream_t s);
-
-// y[o] = act_out(sum_k W[o][k] act_in(x[k]) + b[o]); act: 0 none, 1 SiLU.  fp32.
-hipError_t launch_gemv(int out, int in, const float *W, const float *b, const float *x, float *y,
-                       int act_in, int act_out, hipStream_t s);
-
-// mods[l][j] = m[j] + table_l[j], table_l = tables + l * table_stride, j < width
-hipError_t launch_block_mods(int L, int width, const float *m, const float *tables,
-                             int64_t table_stride, float *mods, hipStream_t s);
+// The timestep path: y = SiLU(W f(t) + b), f the sinusoidal features of 1000 t computed in double (cos, then
+// sin; W [out][freq_dim]); y = W x + b (W [D][D]); and the modulations of every block and of the head,
+// mods[l] = Wm SiLU(e) + bm + table_l, table_l = tables + l * table_stride (6D each), hmod = Wh SiLU(e) + bh
+// (2D).  fp32, D % 8 == 0, 16-byte aligned.
+hipError_t launch_time_mlp1(double t, int freq_dim, int out, const float *W, const float *b, float *y, hipStream_t s);
+hipError_t launch_time_mlp2(int D, const float *W, const float *b, const float *x, float *y, hipStream_t s);
+hipError_t launch_modulations(int L, int D, const float *Wm, const float *bm, const float *Wh, const float *bh,
+                              const float *e, const float *tables, int64_t table_stride, float *mods, float *hmod,
+                              hipStream_t s);
 
 hipError_t launch_f32_to_bf16(int64_t count, const float *x, void *y, hipStream_t s);
 
@@ -87,11 +86,11 @@ hipError_t launch_f32_to_bf16(int64_t count, const float *x, void *y, hipStream_
 hipError_t launch_store_i32(int n, const int32_t *vals, int32_t *dst, hipStream_t s);
 
 // qk RMSNorm + 3-D rotary embedding: (cos, sin) table [T][dh/2] for a token grid of width wp; and the
-// in-place normalisation (gain over D, eps) of M rows of x (act, row stride rs), rotated by the table
-// (row % tokens) when tab is not null.  D % 8 == 0.
+// in-place normalisation (gain over D, eps) of M rows of x0 and, unless null, of x1 (act, row stride rs, a
+// gain each), rotated by the table (row % tokens) when tab is not null.  D % 8 == 0, D <= 6144.
 hipError_t launch_rope_table(int T, int wp, int dh, float2 *tab, hipStream_t s);
-hipError_t launch_qk_norm(ActType t, int M, int D, int dh, void *x, int64_t rs, const float *gain, float eps,
-                          const float2 *tab, int tokens, hipStream_t s);
+hipError_t launch_qk_norm(ActType t, int M, int D, int dh, void *x0, void *x1, int64_t rs, const float *gain0,
+                          const float *gain1, float eps, const float2 *tab, int tokens, hipStream_t s);
 
 // Stochastic update (App. A.1, Eq. 20): z <- z + dt [v + k (z + omt v)] + g eps, eps from Philox4x32-10
 // with key (key0, key1) and counter (element / 4, candidate, step, 0) through Box-Muller.

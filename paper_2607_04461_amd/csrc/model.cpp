@@ -113,18 +113,21 @@ size_t scratch_layout(const Model *m, int rows, int tokens, int text_rows, char 
   char *h = carve(M * D * 4), *act = carve(M * D * a), *qkv = carve(M * 3 * D * a), *o = carve(M * D * a),
        *u = carve(M * F * a), *tok = carve(M * P * a), *vtok = carve(M * P * 4),
        *txt = carve(m->act == ACT_BF16 ? (size_t)text_rows * m->Dt * a : 0), *ctx = carve((size_t)text_rows * D * a),
-       *tf = carve(m->fd * 4), *e1 = carve(D * 4), *e = carve(D * 4), *m6 = carve(6 * D * 4),
+       *e1 = carve(D * 4), *e = carve(D * 4),
        *bm = carve((size_t)m->L * 6 * D * 4), *hm = carve(2 * D * 4), *cond = carve((size_t)rows * 4),
        *rope = carve(m->c.qk_norm_rope ? (size_t)tokens * (m->dh / 2) * 8 : 0),
        *part = carve(m->act == ACT_BF16 ? kSplitBytes : 0);
   if (B) {
     B->h = (float *)h; B->a = act; B->qkv = qkv; B->o = o; B->u = u; B->tok = tok; B->vtok = (float *)vtok;
-    B->txt = txt; B->ctx = ctx; B->tf = (float *)tf; B->e1 = (float *)e1; B->e = (float *)e; B->m6 = (float *)m6;
+    B->txt = txt; B->ctx = ctx; B->e1 = (float *)e1; B->e = (float *)e;
     B->bmods = (float *)bm; B->hmod = (float *)hm; B->d_cond = (int32_t *)cond;
     B->rope = m->c.qk_norm_rope ? (float2 *)rope : nullptr;
     B->part = m->act == ACT_BF16 ? part : nullptr;
     B->part_bytes = m->act == ACT_BF16 ? kSplitBytes : 0;
   }
+  // Two small buffers of earlier step paths still count, so that the sizes the limit refuses stay the same.
+  carve(m->fd * 4);
+  carve(6 * D * 4);
   return off;
 }
 
@@ -205,7 +208,7 @@ flashbon_status flashbon_init_model(const flashbon_model_config *cfg, const floa
   size_t o_h = carve(M * D * 4), o_a = carve(M * D * a), o_qkv = carve(M * 3 * D * a),
          o_o = carve(M * D * a), o_u = carve(M * F * a), o_tok = carve(M * P * a),
          o_txt = carve(m->act == ACT_BF16 ? txt_rows * m->Dt * a : 0), o_ctx = carve(txt_rows * D * a),
-         o_tf = carve(m->fd * 4), o_e1 = carve(D * 4), o_e = carve(D * 4), o_m6 = carve(6 * D * 4),
+         o_e1 = carve(D * 4), o_e = carve(D * 4),
          o_bm = carve((size_t)m->L * 6 * D * 4), o_hm = carve(2 * D * 4), o_cond = carve(cfg->max_n * 4),
          o_v = carve(M * P * 4),
          o_rope = carve(cfg->qk_norm_rope ? (size_t)cfg->max_tokens * (D / cfg->heads / 2) * 8 : 0),
@@ -216,8 +219,8 @@ flashbon_status flashbon_init_model(const flashbon_model_config *cfg, const floa
   StepBufs &B = m->bufs;
   B.h = (float *)(w + o_h); B.a = w + o_a; B.qkv = w + o_qkv; B.o = w + o_o; B.u = w + o_u;
   B.tok = w + o_tok; B.txt = w + o_txt; B.ctx = w + o_ctx;
-  B.tf = (float *)(w + o_tf); B.e1 = (float *)(w + o_e1); B.e = (float *)(w + o_e);
-  B.m6 = (float *)(w + o_m6); B.bmods = (float *)(w + o_bm); B.hmod = (float *)(w + o_hm);
+  B.e1 = (float *)(w + o_e1); B.e = (float *)(w + o_e);
+  B.bmods = (float *)(w + o_bm); B.hmod = (float *)(w + o_hm);
   B.d_cond = (int32_t *)(w + o_cond); B.vtok = (float *)(w + o_v);
   if (cfg->qk_norm_rope) B.rope = (float2 *)(w + o_rope);
   if (m->act == ACT_BF16) { B.part = w + o_part; B.part_bytes = kSplitBytes; }
@@ -438,19 +441,16 @@ static flashbon_status run_step(Model *m, const flashbon_step_args *a, bool draf
       k.out = (char *)a->text_kv + (size_t)l * kv_block * asz; k.ldo = 2 * D; k.bias = Bp(m->lay.blk[l].bkvc);
       HIPCHK(timed(m, tmask, FLASHBON_SITE_TEXT, s, [&] { return lin(act, EPI_STORE, NC * Lt, 2 * D, D, B.ctx, Wp(m->lay.blk[l].wkvc), k, s); }), "text K/V");
       if (c.qk_norm_rope)
-        HIPCHK(timed(m, tmask, FLASHBON_SITE_TEXT, s, [&] { return launch_qk_norm(act, NC * Lt, D, m->dh, k.out, 2 * D, Bp(m->lay.blk[l].nkc), c.ln_eps, nullptr, 1, s); }),
+        HIPCHK(timed(m, tmask, FLASHBON_SITE_TEXT, s, [&] { return launch_qk_norm(act, NC * Lt, D, m->dh, k.out, nullptr, 2 * D, Bp(m->lay.blk[l].nkc), nullptr, c.ln_eps, nullptr, 1, s); }),
                "text key RMSNorm");
     }
   }
 
   // timestep conditioning, shared by all candidates
-  HIPCHK(timed(m, tmask, FLASHBON_SITE_TIME, s, [&] { return launch_time_features((double)a->t_cur, m->fd, B.tf, s); }), "time features");
-  HIPCHK(timed(m, tmask, FLASHBON_SITE_TIME, s, [&] { return launch_gemv(D, m->fd, m->w32 + m->lay.t_w1, Bp(m->lay.t_b1), B.tf, B.e1, 0, 1, s); }), "time mlp 1");
-  HIPCHK(timed(m, tmask, FLASHBON_SITE_TIME, s, [&] { return launch_gemv(D, D, m->w32 + m->lay.t_w2, Bp(m->lay.t_b2), B.e1, B.e, 0, 0, s); }), "time mlp 2");
-  HIPCHK(timed(m, tmask, FLASHBON_SITE_TIME, s, [&] { return launch_gemv(6 * D, D, m->w32 + m->lay.mod_w, Bp(m->lay.mod_b), B.e, B.m6, 1, 0, s); }), "modulation");
-  HIPCHK(timed(m, tmask, FLASHBON_SITE_TIME, s, [&] { return launch_gemv(2 * D, D, m->w32 + m->lay.hmod_w, Bp(m->lay.hmod_b), B.e, B.hmod, 1, 0, s); }), "head modulation");
-  HIPCHK(timed(m, tmask, FLASHBON_SITE_TIME, s, [&] { return launch_block_mods(L, 6 * D, B.m6, m->w32 + m->lay.blk[0].mod, (int64_t)m->lay.block_stride, B.bmods, s); }),
-         "block modulation");
+  HIPCHK(timed(m, tmask, FLASHBON_SITE_TIME, s, [&] { return launch_time_mlp1((double)a->t_cur, m->fd, D, m->w32 + m->lay.t_w1, Bp(m->lay.t_b1), B.e1, s); }), "time mlp 1");
+  HIPCHK(timed(m, tmask, FLASHBON_SITE_TIME, s, [&] { return launch_time_mlp2(D, m->w32 + m->lay.t_w2, Bp(m->lay.t_b2), B.e1, B.e, s); }), "time mlp 2");
+  HIPCHK(timed(m, tmask, FLASHBON_SITE_TIME, s, [&] { return launch_modulations(L, D, m->w32 + m->lay.mod_w, Bp(m->lay.mod_b), m->w32 + m->lay.hmod_w, Bp(m->lay.hmod_b), B.e, m->w32 + m->lay.blk[0].mod, (int64_t)m->lay.block_stride, B.bmods, B.hmod, s); }),
+         "modulation");
 
   // rotary table of this latent size (kept in the model workspace while the size does not change; made
   // on every call in scratch)
@@ -528,8 +528,7 @@ static flashbon_status run_step(Model *m, const flashbon_step_args *a, bool draf
     }
     if (c.qk_norm_rope) {
       void *kp = (char *)B.qkv + (size_t)D * asz;
-      HIPCHK(timed(m, tmask, FLASHBON_SITE_NORM, s, [&] { return launch_qk_norm(act, (int)M, D, dh, B.qkv, 3 * D, Bp(b.nq), c.ln_eps, B.rope, T, s); }), "q RMSNorm + rotary");
-      HIPCHK(timed(m, tmask, FLASHBON_SITE_NORM, s, [&] { return launch_qk_norm(act, (int)M, D, dh, kp, 3 * D, Bp(b.nk), c.ln_eps, B.rope, T, s); }), "k RMSNorm + rotary");
+      HIPCHK(timed(m, tmask, FLASHBON_SITE_NORM, s, [&] { return launch_qk_norm(act, (int)M, D, dh, B.qkv, kp, 3 * D, Bp(b.nq), Bp(b.nk), c.ln_eps, B.rope, T, s); }), "q and k RMSNorm + rotary");
     }
     {
       AttnArgs at;
@@ -552,7 +551,7 @@ static flashbon_status run_step(Model *m, const flashbon_step_args *a, bool draf
       HIPCHK(timed(m, tmask, FLASHBON_SITE_CROSS_Q, s, [&] { return lin(act, EPI_STORE, (int)M, D, D, B.a, Wp(b.wqc), e, s); }), "cross q projection");
     }
     if (c.qk_norm_rope)
-      HIPCHK(timed(m, tmask, FLASHBON_SITE_NORM, s, [&] { return launch_qk_norm(act, (int)M, D, dh, B.qkv, D, Bp(b.nqc), c.ln_eps, nullptr, T, s); }), "cross q RMSNorm");
+      HIPCHK(timed(m, tmask, FLASHBON_SITE_NORM, s, [&] { return launch_qk_norm(act, (int)M, D, dh, B.qkv, nullptr, D, Bp(b.nqc), nullptr, c.ln_eps, nullptr, T, s); }), "cross q RMSNorm");
     {
       const char *kv = (const char *)a->text_kv + (size_t)l * kv_block * asz;
       AttnArgs at;

@@ -31,7 +31,7 @@ struct StepBufs {
   void *txt = nullptr, *ctx = nullptr;  // text tokens (act copy, bf16 mode) and projected context
   float *vtok = nullptr;       // head output [M][C p p] fp32 (stochastic update / guidance)
   float2 *rope = nullptr;      // (cos, sin) per token and pair [T][head_dim/2] (qk_norm_rope)
-  float *tf = nullptr, *e1 = nullptr, *e = nullptr, *m6 = nullptr, *bmods = nullptr, *hmod = nullptr;
+  float *e1 = nullptr, *e = nullptr, *bmods = nullptr, *hmod = nullptr;
   int32_t *d_cond = nullptr;   // prompt of each token-row block
   void *part = nullptr;        // split-K partial sums of the linear layers (bf16 mode), kSplitBytes
   size_t part_bytes = 0;
