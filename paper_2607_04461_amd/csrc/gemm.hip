@@ -63,7 +63,8 @@ __device__ __forceinline__ void euler2(const EpiArgs &e, int64_t zi, float v0, f
 
 template <int EPI, typename TO>
 __device__ __forceinline__ void epilogue4(const EpiArgs &e, int m, int n, float v0, float v1,
-                                          float v2, float v3) {
+                                          float v2, float v3, const f32x4 *residual = nullptr) {
+  // residual: RESIDUAL's input row, where the caller has read it
   float v[4] = {v0, v1, v2, v3};
   if (e.bias) {
     float4 b = *reinterpret_cast<const float4 *>(e.bias + n);
@@ -86,7 +87,9 @@ __device__ __forceinline__ void epilogue4(const EpiArgs &e, int m, int n, float 
     *reinterpret_cast<float4 *>(o) = make_float4(v[0], v[1], v[2], v[3]);
   } else if constexpr (EPI == EPI_RESIDUAL) {
     float *o = reinterpret_cast<float *>(e.out) + (int64_t)m * e.ldo + n;
-    float4 h = *reinterpret_cast<const float4 *>(e.res_in ? e.res_in + (int64_t)m * e.ldo + n : o);
+    float4 h;
+    if (residual) h = make_float4((*residual)[0], (*residual)[1], (*residual)[2], (*residual)[3]);
+    else h = *reinterpret_cast<const float4 *>(e.res_in ? e.res_in + (int64_t)m * e.ldo + n : o);
     if (e.gate) {
       float4 g = *reinterpret_cast<const float4 *>(e.gate + n);
       h.x += g.x * v[0]; h.y += g.y * v[1]; h.z += g.z * v[2]; h.w += g.w * v[3];
@@ -515,6 +518,67 @@ __device__ __forceinline__ void store_staged_f32(const EpiArgs &e, const f32x4 (
 #pragma unroll
       for (int q = 0; q < 4; ++q) o[q] = a[q] + bb[q];
       st4<POL>(rsO, cn == OUT_OF_RANGE ? OUT_OF_RANGE : r0 + (uint32_t)t * rstep + cn, o);
+    }
+  }
+}
+
+// The pixels of a pixel row of token x0 + 2 lanes' tokens, NZ pixel rows of a wave (every `step`-th from `first`):
+// read before the sums they are updated by.  p = 2; lanes 2 x and 2 x + 1 hold the two pixels of token x.
+template <int NZ>
+struct EulerPixels {
+  float z[NZ];
+  EulerRow row;
+  int n0, first, step, last;   // columns n0 + 2 cd + (lane & 1), cd = first + step x < last
+  bool live;
+  __device__ __forceinline__ EulerPixels(const EpiArgs &e, int M, int N, int m, int n0_, int width, int first_, int step_)
+      : row(e, min(m, M - 1)), n0(n0_), first(first_), step(step_), last(min(width, N - n0_) / 2), live(m < M) {
+#pragma unroll
+    for (int x = 0; x < NZ; ++x)
+      if (live && first + step * x < last) z[x] = e.z[at(e, x)];
+  }
+  __device__ __forceinline__ int64_t at(const EpiArgs &e, int x) const {
+    const int cd = first + step * x;
+    return row.at(e, (n0 >> 2) + (cd >> 1), cd & 1) + (threadIdx.x & 1);
+  }
+  // value(column of the tile): the sum and bias
+  template <typename V> __device__ __forceinline__ void update(const EpiArgs &e, V value) const {
+    if (!live) return;
+#pragma unroll
+    for (int x = 0; x < NZ; ++x) {
+      if (first + step * x >= last) break;
+      const float v = value(2 * (first + step * x) + (threadIdx.x & 1));
+      const int64_t zi = at(e, x);
+      if (e.preview) e.preview[zi] = z[x] - e.t_cur * v;
+      e.z[zi] = z[x] + e.dt * v;
+    }
+  }
+};
+
+// Latent update of the 8-wave tile (2 x 4 waves of (16 WTA) x (16 WT)) through LDS: the whole tile is written
+// as fp32 rows and walked along the latent's pixel rows, 32 tokens a wave at a time.
+template <int WTA, int WT>
+__device__ __forceinline__ void euler_staged(const EpiArgs &e, const f32x4 (&acc)[WT][WTA], int M, int N, int m0, int n0,
+                                             int wm, int wn, int fr, int fq, int lane, int wave, char *lds) {
+  constexpr int BM = 32 * WTA, BN = 64 * WT, LDR = BN + 4, NZ = BN / 2 / 8;
+  float *t = reinterpret_cast<float *>(lds);
+  __syncthreads();   // every wave is past its last fragment reads: the ring is free
+#pragma unroll
+  for (int i = 0; i < WT; ++i)
+#pragma unroll
+    for (int j = 0; j < WTA; ++j)   // fragments 2 a and 2 a + 1: columns 32 a + 8 fq .. + 7 of the wave
+      *reinterpret_cast<f32x4 *>(t + (16 * WTA * wm + 16 * j + fr) * LDR + 16 * WT * wn + 32 * (i >> 1) + 8 * fq + 4 * (i & 1)) = acc[i][j];
+  __syncthreads();
+  auto value = [&](int row, int col) { return e.bias ? t[row * LDR + col] + e.bias[n0 + col] : t[row * LDR + col]; };
+  if (e.p == 2) {
+    for (int r0 = 0; r0 < BM && m0 + r0 < M; r0 += 32) {
+      const int row = r0 + (lane >> 1);
+      const EulerPixels<NZ> px(e, M, N, m0 + row, n0, BN, wave, 8);
+      px.update(e, [&](int col) { return value(row, col); });
+    }
+  } else {
+    for (int x = threadIdx.x; x < BM * BN; x += 512) {
+      const int row = x / BN, col = x % BN;
+      if (m0 + row < M && n0 + col < N) euler1(e, EulerRow(e, m0 + row).of_column(e, n0 + col), value(row, col));
     }
   }
 }
@@ -1035,7 +1099,10 @@ __device__ __forceinline__ void dma8_tile(int M, int N, int K, const bf16 *__res
   }
   substep(T_{}, F_{}, fw0, fa0, last, 1, fw1, fa1, 0, 0);
   substep(F_{}, F_{}, fw1, fa1, 0, 0, fw0, fa0, 0, 0);
-  if constexpr (EPI == EPI_RESIDUAL && 8 * 16 * WTA * 32 * 4 <= NST * STAGE * 2) {
+  if constexpr (EPI == EPI_EULER) {
+    static_assert(BM * (BN + 4) * 4 <= NST * STAGE * 2, "the tile fits the ring");
+    euler_staged<WTA, WT>(e, acc, M, N, m0, n0, wm, wn, fr, fq, lane, wave, reinterpret_cast<char *>(smem));
+  } else if constexpr (EPI == EPI_RESIDUAL && 8 * 16 * WTA * 32 * 4 <= NST * STAGE * 2) {
     // the ring (NST stages of (32 WTA + 64 WT) x 64 bf16) holds the 8 waves' (16 WTA) x 32 fp32 blocks
     // (all tiles but 160 x 128 with 2 stages)
     char *lw = reinterpret_cast<char *>(smem);
@@ -1159,20 +1226,17 @@ __global__ __launch_bounds__(256, 1) void k_linear_dma(int M, int N, int K, cons
   }
   dma_tile<EPI, TO, WTA>(M, N, K, A, Wt, e, m0, n0, smem);
 }
-// -------------------------------------------------------------------------- few output columns
-// The head of the network with the latent update: bf16 operands, 32 rows x 64 columns per workgroup (all of
-// a head's columns at C p^2 = 64), one pass over A.  The waves take the K chunks of 64 in turn, their
-// fragments straight from memory (a lane's 16 bytes of A and W rows are the MFMA operands), one chunk ahead;
-// the sums are added through LDS in wave order, and the tile is then walked along the latent's rows, whose
-// pixels were read at the start.  Four waves, three workgroups a CU; eight where the tiles leave CUs idle.
-// Bound by A's rows at many tokens and by the chain of loads at few: K = 1536 with 24960 rows 44 us, K = 256
-// with 390 rows 5.4 us.  The 128x128 and 256x256 tiles of the other layers, with four divisions an
-// output in their epilogue, took 58 and 53 us; with the pixels read after the sums this kernel took 50 and 7.
+// ------------------------------------------------------------------------- few output tiles, bf16
+// 32 rows x 64 columns per workgroup for layers with at most one such tile per CU, the head with its latent
+// update (EPI_EULER) among them.  Eight waves take the K chunks of 64 in turn, their fragments straight from
+// memory (a lane's 16 bytes of A and W rows are the MFMA operands), one chunk ahead; the sums are added
+// through LDS in wave order.  What the epilogue reads (pixels, residual rows) is read before the sums.  Bound by
+// the chain of loads, which 128x128 tiles stretch over more K tiles and fewer CUs; times at the dispatch.
 namespace nar {
-constexpr int BM = 32, BN = 64, LDR = BN + 4;   // LDR: floats of a row of sums
+constexpr int BM = 32, BN = 64, WAVES = 8, LDR = BN + 4;   // LDR: floats of a row of sums
 }
-template <int WAVES>
-__global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 2 : 3) void k_linear_head(int M, int N, int K, const bf16 *__restrict__ A,
+template <int EPI>
+__global__ __launch_bounds__(64 * nar::WAVES, 2) void k_linear_narrow(int M, int N, int K, const bf16 *__restrict__ A,
                                                                const bf16 *__restrict__ Wt, EpiArgs e) {
   using namespace nar;
   __shared__ __attribute__((aligned(16))) float sums[WAVES][BM][LDR];
@@ -1210,23 +1274,20 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 2 : 3) void k_linear_head(
           acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fw[buf][i][h]),
                                                               __builtin_bit_cast(bf16x8, fa[buf][j][h]), acc[i][j], 0, 0, 0);
   };
-  // p = 2, lanes 2 x, 2 x + 1: the two pixels of a pixel row of token x; a wave takes the pixel rows in turn.
-  // The latents are read now, so that their latency passes under the sums.
-  constexpr int NZ = BN / 2 / WAVES;
-  const int tok = m0 + (lane >> 1), dj = lane & 1;
-  const bool pairs = e.p == 2;
-  float z[NZ];
-  int64_t zi[NZ];
-  if (pairs && tok < M) {
-    const EulerRow r(e, tok);
-#pragma unroll
-    for (int x = 0; x < NZ; ++x) {
-      const int cd = wave + WAVES * x;
-      zi[x] = r.at(e, (n0 >> 2) + (cd >> 1), cd & 1) + dj;
-      if (n0 + 2 * cd < N) z[x] = e.z[zi[x]];
-    }
-  }
   if (wave < chunks) load(wave, 0);
+  // EULER with p = 2: a wave takes every eighth pixel row of the tile's 32 tokens.  Other epilogues: a
+  // thread's 4 columns of one row.
+  const bool pairs = EPI == EPI_EULER && e.p == 2;
+  const int row = pairs ? lane >> 1 : tid >> 4, m = m0 + row, n = n0 + 4 * (tid & 15);
+  auto pixels = [&] {
+    if constexpr (EPI == EPI_EULER) return EulerPixels<BN / 2 / WAVES>(e, M, N, pairs ? m : M, n0, BN, wave, WAVES);
+    else return 0;
+  };
+  const auto px = pixels();
+  f32x4 h;
+  if constexpr (EPI == EPI_RESIDUAL) {
+    if (m < M && n < N) h = *reinterpret_cast<const f32x4 *>((e.res_in ? e.res_in : (const float *)e.out) + (int64_t)m * e.ldo + n);
+  }
   for (int ch = wave; ch < chunks; ch += 2 * WAVES) {
     if (ch + WAVES < chunks) load(ch + WAVES, 1);
     mul(0);
@@ -1240,26 +1301,25 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 2 : 3) void k_linear_head(
     for (int j = 0; j < 2; ++j) *reinterpret_cast<f32x4 *>(&sums[wave][16 * j + fr][16 * i + 4 * fq]) = acc[i][j];
   __syncthreads();
   const int used = min(WAVES, chunks);
-  auto value = [&](int row, int col) {
-    float v = sums[0][row][col];
-    for (int w = 1; w < used; ++w) v += sums[w][row][col];
-    return e.bias ? v + e.bias[n0 + col] : v;
-  };
-  if (pairs) {
-    if (tok >= M) return;
-#pragma unroll
-    for (int x = 0; x < NZ; ++x) {
-      const int cd = wave + WAVES * x;
-      if (n0 + 2 * cd >= N) break;
-      const float v = value(lane >> 1, 2 * cd + dj);
-      if (e.preview) e.preview[zi[x]] = z[x] - e.t_cur * v;
-      e.z[zi[x]] = z[x] + e.dt * v;
+  if constexpr (EPI == EPI_EULER) {
+    auto value = [&](int row, int col) {
+      float v = sums[0][row][col];
+      for (int w = 1; w < used; ++w) v += sums[w][row][col];
+      return e.bias ? v + e.bias[n0 + col] : v;
+    };
+    if (pairs) {
+      px.update(e, [&](int col) { return value(row, col); });
+    } else {
+      for (int x = tid; x < BM * BN; x += 64 * WAVES) {
+        const int r = x / BN, col = x % BN;
+        if (m0 + r < M && n0 + col < N) euler1(e, EulerRow(e, m0 + r).of_column(e, n0 + col), value(r, col));
+      }
     }
   } else {
-    for (int x = tid; x < BM * BN; x += 64 * WAVES) {
-      const int row = x / BN, col = x % BN;
-      if (m0 + row < M && n0 + col < N) euler1(e, EulerRow(e, m0 + row).of_column(e, n0 + col), value(row, col));
-    }
+    if (m >= M || n >= N) return;
+    f32x4 v = *reinterpret_cast<const f32x4 *>(&sums[0][row][n - n0]);
+    for (int w = 1; w < used; ++w) v += *reinterpret_cast<const f32x4 *>(&sums[w][row][n - n0]);
+    epilogue4<EPI, bf16>(e, m, n, v[0], v[1], v[2], v[3], EPI == EPI_RESIDUAL ? &h : nullptr);
   }
 }
 
@@ -1480,7 +1540,7 @@ __global__ __launch_bounds__(256) void k_linear_valu_dot(int M, int N, int K, co
 // == 0, K >= 128, N % 8 == 0) the 256-column tiles run on the 8-wave kernel, which measured 6-7%
 // faster than the 4-wave kernel on the same tiles at every projection of the draft; the 4-wave
 // kernel is kept for forced plans.
-enum TilePlan { PLAN_BIG, PLAN_SMALL, PLAN_SPLIT, PLAN_MIX, PLAN_DEEP };
+enum TilePlan { PLAN_BIG, PLAN_SMALL, PLAN_SPLIT, PLAN_MIX, PLAN_DEEP, PLAN_NARROW };
 struct TileChoice {
   TilePlan plan;
   int wta;    // PLAN_MIX: the taller height, 32 wta rows
@@ -1491,6 +1551,10 @@ struct TileChoice {
   int wt = 4, nst = 2;   // PLAN_DEEP: (32 wta) x (64 wt) tiles, nst LDS stages
 };
 static int cu_count();
+// Whether a layer is at most one 32x64 tile per CU and its K whole MFMA steps.
+static bool narrow_fits(int M, int N, int K) {
+  return K % 32 == 0 && (int64_t)((M + 31) / 32) * ((N + 63) / 64) <= cu_count();
+}
 // The deep-ring tiles (wta, wt) in the order the plans try them: 128 x 128, 160 x 128, 128 x 256, 160 x 256.
 static constexpr int kDeepTiles[4][2] = {{4, 2}, {5, 2}, {4, 4}, {5, 4}};
 // The deep-ring instantiations: 128 or 160 rows x 128 or 256 columns, 2 or 3 LDS stages.
@@ -1525,6 +1589,7 @@ static TileChoice pick_tiles(int M, int N, int K, bool dma_ok) {
   // (k_linear_deep: rows 128 or 160, cols 128 or 256, 2 or 3 LDS stages)
   const char *force = getenv("FLASHBON_LINEAR_TILE");
   if (force) {
+    if (!strcmp(force, "narrow")) return {PLAN_NARROW, 0, 0, 0, 0, 8};
     if (dma_ok && !strncmp(force, "deep:", 5)) {
       int rows = 0, cols = 0, nst = 0;
       if (sscanf(force + 5, "%d:%d:%d", &rows, &cols, &nst) == 3 && deep_ok(rows / 32, cols / 64, nst) &&
@@ -1564,6 +1629,11 @@ static TileChoice pick_tiles(int M, int N, int K, bool dma_ok) {
     }
     return {strcmp(force, "128x128") ? PLAN_BIG : PLAN_SMALL, 8, 0, 0, 0};
   }
+  // At most one 32x64 tile a CU: k_linear_narrow.  Against 128x128 tiles (the K >= 128 shapes, us): (390, 256, 256)
+  // 4.2 and 5.5, (390, 704, 256) 4.2 and 5.8, (390, 256, 704) 6.5 and 7.8, (16, 8960, 1536) 10.2 and 12.3,
+  // (256, 1536, 1536) 11.9 and 12.2; beyond it falls back ((390, 1536, 256), 312 tiles, 6.0 and 5.8; (256, 4608,
+  // 1536), 576 tiles, 30 and 13).
+  if (narrow_fits(M, N, K)) return {PLAN_NARROW, 0, 0, 0, 0, 8};
   constexpr double kSmallA = 0.704, kSmallFix = 604.0;
   const int cus = cu_count();
   auto rounds = [&](int64_t tiles, int per_cu) { return (double)((tiles + per_cu * cus - 1) / (per_cu * cus)); };
@@ -1810,11 +1880,19 @@ static hipError_t launch_f32(int M, int N, int K, const float *A, const float *W
   return hipGetLastError();
 }
 
+template <int EPI>
+static hipError_t launch_narrow(int M, int N, int K, const void *A, const void *Wt, const EpiArgs &e, hipStream_t s) {
+  const dim3 grid((M + nar::BM - 1) / nar::BM, (N + nar::BN - 1) / nar::BN);
+  hipLaunchKernelGGL(k_linear_narrow<EPI>, grid, dim3(64 * nar::WAVES), 0, s, M, N, K, (const bf16 *)A, (const bf16 *)Wt, e);
+  return hipGetLastError();
+}
+
 // bf16 operands, every epilogue but the latent scatter.
 template <int EPI>
 static hipError_t launch_bf16(int M, int N, int K, const void *A, const void *Wt, const EpiArgs &e, hipStream_t s) {
   const bool dma_ok = K % mf::BK == 0 && K >= 2 * mf::BK && N % 8 == 0;
   const TileChoice c = pick_tiles(M, N, K, dma_ok);
+  if (c.plan == PLAN_NARROW) return launch_narrow<EPI>(M, N, K, A, Wt, e, s);
   if (c.plan == PLAN_SMALL) return launch_mfma<4, 4, 2, 2, EPI, 2>(M, N, K, A, Wt, e, s);
   if (c.plan == PLAN_BIG) return launch_big<EPI>(M, N, K, A, Wt, e, s);
   if (c.plan == PLAN_DEEP) {
@@ -1852,11 +1930,11 @@ static hipError_t launch_epi(ActType t, int M, int N, int K, const void *A, cons
                              const EpiArgs &e, hipStream_t s) {
   if (t == ACT_BF16) {
     if constexpr (EPI == EPI_EULER) {
-      const dim3 grid((M + nar::BM - 1) / nar::BM, (N + nar::BN - 1) / nar::BN);
-      const bool wide = (int64_t)grid.x * grid.y <= cu_count();
-      hipLaunchKernelGGL(wide ? k_linear_head<8> : k_linear_head<4>, grid, dim3(wide ? 512 : 256), 0, s, M, N, K,
-                         (const bf16 *)A, (const bf16 *)Wt, e);
-      return hipGetLastError();
+      // the head: its columns are one tile wide, so past one 32x64 tile a CU the 128x128 tile's whole-row loads
+      // stream A better (24960 rows of K = 1536: 28 us, 44 on 32x64 tiles; 58 on 128x128 tiles with four divisions an output)
+      const bool dma_ok = K % mf::BK == 0 && K >= 2 * mf::BK && N % 8 == 0;
+      if (dma_ok && !narrow_fits(M, N, K)) return launch_deep<EPI, 4, 2, 3>(M, N, K, A, Wt, e, s);
+      return launch_narrow<EPI>(M, N, K, A, Wt, e, s);
     } else {
       return launch_bf16<EPI>(M, N, K, A, Wt, e, s);
     }
@@ -1882,7 +1960,7 @@ int describe_linear(ActType t, int epi, int M, int N, int K, char *buf, int len)
   int kernels = 1;
   auto rows_of = [](int w) { return std::to_string(32 * w); };
   if (t == ACT_BF16 && epi == EPI_EULER) {
-    d = "k_linear_head: 32x64 tiles, K over 8 waves";
+    d = "k_linear_narrow or k_linear_deep with the latent update";
   } else if (t != ACT_BF16) {
     switch (f32_tile(M, N, K, true)) {   // operands on 16 bytes
       case F32_MID: d = "k_linear_f32: 64x64 tiles, fp32 matrix cores"; break;
@@ -1894,7 +1972,9 @@ int describe_linear(ActType t, int epi, int M, int N, int K, char *buf, int len)
     const bool dma_ok = K % mf::BK == 0 && K >= 2 * mf::BK && N % 8 == 0;
     const TileChoice c = pick_tiles(M, N, K, dma_ok);
     const std::string nt = std::to_string((N + 255) / 256);
-    if (c.plan == PLAN_DEEP) {
+    if (c.plan == PLAN_NARROW) {
+      d = "k_linear_narrow: 32x64 tiles, K over 8 waves";
+    } else if (c.plan == PLAN_DEEP) {
       d = "k_linear_deep (8 waves): " + rows_of(c.wta) + "x" + std::to_string(64 * c.wt) + " tiles, " +
           std::to_string(c.nst) + " LDS stages";
     } else if (c.plan == PLAN_SMALL) {
@@ -2021,6 +2101,111 @@ hipError_t launch_linear_ws(ActType t, int epi, int M, int N, int K, const void 
     case EPI_RESIDUAL: hipLaunchKernelGGL(k_splitk_reduce<EPI_RESIDUAL>, grid, dim3(256), 0, s, M, N, sp, part, e); break;
     default: return hipErrorInvalidValue;
   }
+  return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------- patch embedding, bf16
+// out[m][n] (fp32) = patch of token m . W[n] + bias[n] for patches of at most 64 features, read where they lie
+// in the latents (rounded to bf16 as operands).  A wave keeps the weights of 64 columns in registers and takes
+// `blocks` blocks of 16 tokens, the next block's pixels on their way while it multiplies and stores.  Bound by the
+// fp32 rows it writes: 24960 x 1536 takes 45 us, where a patchify kernel and a 256x256 tile on K = 64 took
+// 54, 390 x 256 4.0 us against 14.
+namespace emb {
+constexpr int WAVES = 4, BN = 64 * WAVES, KMAX = 64;
+}
+template <int P2>   // patch == 2
+__global__ __launch_bounds__(64 * emb::WAVES) void k_embed(int M, int N, int K, int zrows, int C, int H, int W, int p,
+                                                           const float *__restrict__ z, const bf16 *__restrict__ Wt,
+                                                           const float *__restrict__ bias, float *__restrict__ out,
+                                                           int blocks) {
+  using namespace emb;
+  const int lane = threadIdx.x & 63, fr = lane & 15, fq = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n0 = blockIdx.y * BN + 64 * wave, m_first = blockIdx.x * blocks * 16, m_end = min(M, m_first + blocks * 16);
+  if (n0 >= N) return;
+  // fragment i of W: rows n0 + 32 (i / 2) + 8 (fr / 4) + 4 (i % 2) + fr % 4, so that a lane's outputs of fragments
+  // 2 a and 2 a + 1 are 8 consecutive columns n0 + 32 a + 8 fq ..; rows past N and columns past K are zero
+  const __amdgpu_buffer_rsrc_t rsW = epi::rsrc(Wt + (int64_t)n0 * K, (uint32_t)min(N - n0, 64) * (uint32_t)K * 2u);
+  bf16x8 fw[4][2];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int row = 32 * (i >> 1) + 8 * (fr >> 2) + 4 * (i & 1) + (fr & 3), k = 32 * h + 8 * fq;
+      fw[i][h] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(
+                                                rsW, k < K ? (uint32_t)(row * K + k) * 2u : epi::OUT_OF_RANGE, 0, 0));
+    }
+  f32x4 b[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int n = n0 + 32 * (i >> 1) + 8 * fq + 4 * (i & 1);
+    b[i] = bias && n < N ? *reinterpret_cast<const f32x4 *>(bias + n) : f32x4{0, 0, 0, 0};
+  }
+  typedef float f32x2u __attribute__((ext_vector_type(2), aligned(4)));
+  const int wp = W / p, T = (H / p) * wp;
+  const int64_t plane = (int64_t)H * W;
+  float v[2][8];   // the lane's features of its token
+  auto fetch = [&](int m0) {
+    // token m: candidate c (twin rows read the latents of row c % zrows), row i, column j of the patch grid
+    const int m = min(m0 + fr, M - 1), c = m / T, t = m - c * T, i = t / wp, j = t - i * wp;
+    const float *zt = z + ((int64_t)(c % zrows) * C * H + p * i) * W + p * j;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int k = 32 * h + 8 * fq;   // K % 8 == 0
+      if (k >= K) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[h][q] = 0.f;
+      } else if constexpr (P2) {
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {   // pixel row x % 2 of channel k / 4 + x / 2
+          const f32x2u y = *reinterpret_cast<const f32x2u *>(zt + ((k >> 2) + (x >> 1)) * plane + (x & 1) * W);
+          v[h][2 * x] = y[0];
+          v[h][2 * x + 1] = y[1];
+        }
+      } else {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+          const int ch = (k + q) / (p * p), r = (k + q) - ch * p * p, di = r / p;
+          v[h][q] = zt[ch * plane + (int64_t)di * W + (r - di * p)];
+        }
+      }
+    }
+  };
+  if (m_first < m_end) fetch(m_first);
+  for (int m0 = m_first; m0 < m_end; m0 += 16) {
+    bf16x8 fa[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int q = 0; q < 8; ++q) fa[h][q] = (bf16)v[h][q];
+    if (m0 + 16 < m_end) fetch(m0 + 16);
+    f32x4 acc[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[i][0], fa[0], f32x4{0, 0, 0, 0}, 0, 0, 0);
+      acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[i][1], fa[1], acc[i], 0, 0, 0);
+    }
+    const int m = m0 + fr;
+    if (m < m_end) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int n = n0 + 32 * (i >> 1) + 8 * fq + 4 * (i & 1);
+        if (n < N) *reinterpret_cast<f32x4 *>(out + (int64_t)m * N + n) = acc[i] + b[i];   // N % 4 == 0
+      }
+    }
+  }
+}
+
+bool embed_takes(int K) { return K <= emb::KMAX; }
+
+hipError_t launch_embed(int n, int zrows, int C, int H, int W, int p, int D, const float *z, const void *Wt,
+                        const float *bias, float *out, hipStream_t s) {
+  const int M = n * (H / p) * (W / p), K = C * p * p, ct = (D + emb::BN - 1) / emb::BN, rb = (M + 15) / 16;
+  // eight blocks a workgroup amortise the weights; fewer while that leaves under four workgroups a CU
+  const int blocks = (int)std::max<int64_t>(1, std::min<int64_t>(8, (int64_t)rb * ct / (4 * cu_count())));
+  const dim3 grid((rb + blocks - 1) / blocks, ct);
+  auto kern = p == 2 ? k_embed<1> : k_embed<0>;
+  hipLaunchKernelGGL(kern, grid, dim3(64 * emb::WAVES), 0, s, M, D, K, zrows, C, H, W, p, z, (const bf16 *)Wt, bias, out, blocks);
   return hipGetLastError();
 }
 

@@ -68,6 +68,11 @@ hipError_t launch_proxy(int64_t count, const float *h1, const float *h2, const f
 // tokens [n*T][C p p] (act) from z [zrows][C][H][W] fp32; token row block b reads latent b % zrows
 hipError_t launch_patchify(ActType t, int n, int zrows, int C, int H, int W, int p, const float *z, void *tok,
                            hipStream_t s);
+// Patch embedding, bf16, in one launch: out [n*T][D] (fp32) = patches of z (rounded to bf16) . Wt [D][C p p] + bias,
+// row blocks as above, for patches that embed_takes (C p p <= 64).  C p p % 8 == 0, D % 4 == 0.
+bool embed_takes(int patch_dim);
+hipError_t launch_embed(int n, int zrows, int C, int H, int W, int p, int D, const float *z, const void *Wt,
+                        const float *bias, float *out, hipStream_t s);
 
 // The timestep path: y = SiLU(W f(t) + b), f the sinusoidal features of 1000 t computed in double (cos, then
 // sin; W [out][freq_dim]); y = W x + b (W [D][D]); and the modulations of every block and of the head,

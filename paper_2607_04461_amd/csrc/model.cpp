@@ -485,10 +485,14 @@ static flashbon_status run_step(Model *m, const flashbon_step_args *a, bool draf
   // dump then leaves those entries untouched (their values are never formed).
   bool formed = embed_live;
   if (embed_live) {
-    HIPCHK(timed(m, tmask, FLASHBON_SITE_EMBED, s, [&] { return launch_patchify(act, R, a->n, m->C, a->latent_h, a->latent_w, p, a->latents, B.tok, s); }), "patchify");
-    EpiArgs e;
-    e.out = B.h; e.ldo = D; e.bias = Bp(m->lay.pe_b);
-    HIPCHK(timed(m, tmask, FLASHBON_SITE_EMBED, s, [&] { return lin(act, EPI_STORE_F32, (int)M, D, P, B.tok, Wp(m->lay.pe_w), e, s); }), "patch embed");
+    if (act == ACT_BF16 && embed_takes(P)) {
+      HIPCHK(timed(m, tmask, FLASHBON_SITE_EMBED, s, [&] { return launch_embed(R, a->n, m->C, a->latent_h, a->latent_w, p, D, a->latents, Wp(m->lay.pe_w), Bp(m->lay.pe_b), B.h, s); }), "patch embed");
+    } else {
+      HIPCHK(timed(m, tmask, FLASHBON_SITE_EMBED, s, [&] { return launch_patchify(act, R, a->n, m->C, a->latent_h, a->latent_w, p, a->latents, B.tok, s); }), "patchify");
+      EpiArgs e;
+      e.out = B.h; e.ldo = D; e.bias = Bp(m->lay.pe_b);
+      HIPCHK(timed(m, tmask, FLASHBON_SITE_EMBED, s, [&] { return lin(act, EPI_STORE_F32, (int)M, D, P, B.tok, Wp(m->lay.pe_w), e, s); }), "patch embed");
+    }
     if ((st = dump(0)) != FLASHBON_OK) return st;
   }
 

@@ -16,11 +16,12 @@ pytestmark = pytest.mark.gpu
 
 
 # (channels, patch): C p^2 columns = 64, 8 (narrower than a tile), 72 and 128 (a second, partial or whole column
-# tile); the hidden widths 72 and 1088 end inside a K chunk of 64 and give the waves unequal shares
+# tile); the hidden widths 72 and 1088 end inside a K chunk of 64 and give the waves unequal shares; the last three
+# have more than one 32x64 tile per CU and take 128x128 tiles
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
-@pytest.mark.parametrize("channels,patch,hidden,heads,h,w", [(16, 2, 64, 4, 10, 6), (2, 2, 72, 9, 14, 22), (18, 2, 64, 4, 6, 6),
-                                                             (32, 2, 1088, 17, 10, 14), (8, 1, 64, 4, 5, 7),
-                                                             (8, 3, 64, 4, 9, 12), (4, 4, 128, 4, 8, 20)])
+@pytest.mark.parametrize("channels,patch,hidden,heads,h,w", [
+    (16, 2, 64, 4, 10, 6), (2, 2, 72, 9, 14, 22), (18, 2, 64, 4, 6, 6), (32, 2, 1088, 17, 10, 14), (8, 1, 64, 4, 5, 7),
+    (8, 3, 64, 4, 9, 12), (4, 4, 128, 4, 8, 20), (16, 2, 128, 1, 106, 106), (32, 2, 192, 6, 60, 98), (8, 3, 128, 2, 108, 117)])
 def test_head_update_and_preview(dtype, channels, patch, hidden, heads, h, w):
     shape = synth.ModelShape(num_blocks=1, hidden=hidden, heads=heads, mlp_hidden=64, freq_dim=32, text_dim=32,
                              latent_channels=channels, patch=patch)
