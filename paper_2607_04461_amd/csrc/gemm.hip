@@ -648,17 +648,22 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(const bf16 *base, in
 // all n-tiles, so the workgroups resident on one XCD share A rows and W rows in that XCD's L2
 // (group 1: every n-tile of one row block before the next row block).
 constexpr int GROUP_M = 8;
-__device__ __forceinline__ void tile_of(int bid, int MT, int NT, int &mt, int &nt, int group_m = GROUP_M) {
-  const int total = MT * NT;
+// Place of workgroup bid among `total`, contiguous per XCD.
+__device__ __forceinline__ int xcd_place(int bid, int total) {
   const int xcd = bid & 7, local = bid >> 3;
-  const int base = total >> 3, rem = total & 7;
-  const int t = xcd * base + min(xcd, rem) + local;
+  return xcd * (total >> 3) + min(xcd, total & 7) + local;
+}
+// Tile t of the grouped order.
+__device__ __forceinline__ void tile_at(int t, int MT, int NT, int &mt, int &nt, int group_m) {
   const int per_group = group_m * NT;
   const int group = t / per_group, first_m = group * group_m;
   const int gm = min(MT - first_m, group_m);
   const int r = t - group * per_group;
   mt = first_m + r % gm;
   nt = r / gm;
+}
+__device__ __forceinline__ void tile_of(int bid, int MT, int NT, int &mt, int &nt, int group_m = GROUP_M) {
+  tile_at(xcd_place(bid, MT * NT), MT, NT, mt, nt, group_m);
 }
 }  // namespace mf
 
@@ -1161,17 +1166,17 @@ __global__ __launch_bounds__(512, 1) void k_linear_deep(int M, int N, int K, con
 // Split-K: MT x NT tiles of (32 WTA) x (64 WT) on the 8-wave tile with an LDS ring of NST stages, each
 // tile's K range cut into `splits` ranges of ks columns (the last one shorter); workgroup (tile, split)
 // accumulates its range and stores the fp32 partial sums into part + split M N ([M][N] per split, no
-// bias).  k_splitk_reduce then adds the splits in order and applies the epilogue.  For launches whose
-// tiles alone would leave most CUs idle (one candidate's MLP down-projection, K = 8960).
+// bias).  An XCD's workgroups are neighbours in (split, tile) order, so that it reads one or two K ranges and
+// not all of them ((1560, 1536, 8960) 52 -> 49 us).  k_splitk_reduce then adds the splits in order and applies
+// the epilogue.  For launches whose tiles alone would leave most CUs idle (one candidate's MLP down-projection, K = 8960).
 template <int WTA, int WT, int NST>
 __global__ __launch_bounds__(512, 1) void k_linear_splitk(int M, int N, int K, const bf16 *__restrict__ A,
                                                    const bf16 *__restrict__ Wt, float *__restrict__ part,
                                                    int MT, int NT, int ks, int group_m) {
   extern __shared__ __attribute__((aligned(16))) bf16 smem[];
-  const int tiles = MT * NT;
-  const int split = blockIdx.x / tiles;
+  const int tiles = MT * NT, place = mf::xcd_place(blockIdx.x, gridDim.x), split = place / tiles;
   int mt, nt;
-  mf::tile_of(blockIdx.x - split * tiles, MT, NT, mt, nt, group_m);
+  mf::tile_at(place - split * tiles, MT, NT, mt, nt, group_m);
   const int m0 = 32 * WTA * mt, n0 = 64 * WT * nt, k0 = split * ks;
   if (m0 >= M || k0 >= K) return;
   EpiArgs e;
@@ -1730,10 +1735,15 @@ static hipError_t launch_mfma(int M, int N, int K, const void *A, const void *Wt
 // projections at 1 (about 1% ahead of 4), QKV (18 column tiles) at 8, MLP up (35) at 6 (55.8 against
 // 56.5 ms at 8).  The order does not change any output.  FLASHBON_LINEAR_GROUP (tuning): a fixed
 // group height.
-static int group_rows(int MT, int NT, int K) {
+// Launches of one round have orders of their own, all their tiles being at work at once: groups of 5 row blocks
+// for the deep-ring tile ((1560, 1536, 1536) 13.9 us, 14.5 at 8 and 15.1 at 1; (3120, 1536, 8960) 77.0, 77.4 and
+// 77.7), groups of 3 for split-K ((1560, 1536, 8960) 49.0 us, 49.7 at 1 and 49.2 at 8; (500, 5120, 13824) 71.9, 83.2
+// and 69.7; (512, 1536, 4096) 17.3, 17.3 and 19.8).
+constexpr int kDeepGroup = 5, kSplitGroup = 3;
+static int group_rows(int NT, int otherwise = 0) {
   const char *force = getenv("FLASHBON_LINEAR_GROUP");
   if (force && atoi(force) > 0) return atoi(force);
-  (void)MT; (void)K;
+  if (otherwise) return otherwise;
   if (NT <= 8) return 1;
   return NT <= 24 ? mf::GROUP_M : 6;
 }
@@ -1753,7 +1763,7 @@ static hipError_t launch_dma(int M, int N, int K, const void *A, const void *Wt,
   }
   const int NT = (N + 255) / 256;
   hipLaunchKernelGGL(kern, dim3(mb * NT), dim3(256), lds, s, M, N, K, (const bf16 *)A, (const bf16 *)Wt, e,
-                     mb, NT, tall, group_rows(mb, NT, K));
+                     mb, NT, tall, group_rows(NT));
   return hipGetLastError();
 }
 
@@ -1778,7 +1788,7 @@ static hipError_t launch_dma8(int M, int N, int K, const void *A, const void *Wt
   }
   const int NT = (N + 255) / 256;
   hipLaunchKernelGGL(kern, dim3(mb * NT), dim3(512), lds, s, M, N, K, (const bf16 *)A, (const bf16 *)Wt, e, mb, NT,
-                     tall, group_rows(mb, NT, K));
+                     tall, group_rows(NT));
   return hipGetLastError();
 }
 
@@ -1795,7 +1805,7 @@ static hipError_t launch_deep(int M, int N, int K, const void *A, const void *Wt
   }
   const int MT = (M + 32 * WTA - 1) / (32 * WTA), NT = (N + 64 * WT - 1) / (64 * WT);
   hipLaunchKernelGGL(kern, dim3(MT * NT), dim3(512), lds, s, M, N, K, (const bf16 *)A, (const bf16 *)Wt, e, MT, NT,
-                     group_rows(MT, NT, K));
+                     group_rows(NT, kDeepGroup));
   return hipGetLastError();
 }
 
@@ -2011,7 +2021,9 @@ int describe_linear(ActType t, int epi, int M, int N, int K, char *buf, int len)
 // round of the CUs (on a tie, the first tile in kDeepTiles order and the fewest splits).  Measured for one
 // candidate's MLP down-projection (M = 1560, N = 1536, K = 8960, residual epilogue; reduction included):
 // 160 x 128 x 2 ranges (240 workgroups) 53 us, against 62 us for 224 x 256 x 5 ranges on two stages,
-// 56 us for 128 x 256 x 3, 60 us for 160 x 256 x 4 and 63 us unsplit (128 x 128, 156 workgroups).  A
+// 56 us for 128 x 256 x 3, 60 us for 160 x 256 x 4 and 63 us unsplit (128 x 128, 156 workgroups).  Where
+// the unsplit launch has nearly as many workgroups the partial sums cost more than they give: M = 3120 has 240
+// either way and takes 77 us unsplit, 83 split, so a split has to bring a quarter more.  A
 // function of the shape alone, so every caller with a workspace gets the same plan (and the same bits).
 // FLASHBON_SPLITK (tuning): "<rows>:<cols>:<stages>:<splits>" forces a plan on the shapes that split.
 struct SplitPlan {
@@ -2040,16 +2052,17 @@ static SplitPlan splitk_plan(int epi, int M, int N, int K) {
       return {sp, rows / 32, cols / 64, nst};
   }
   SplitPlan best = none;
-  int64_t most = 0;
+  int64_t most = 0, whole = 0;   // workgroups of the plan, and of the deep-ring tile on the whole of K
   for (const auto &d : kDeepTiles) {
     const int64_t t = (int64_t)((M + 32 * d[0] - 1) / (32 * d[0])) * ((N + 64 * d[1] - 1) / (64 * d[1]));
+    if (t <= cus && t > whole) whole = t;
     for (int sp = 2; sp <= K / (16 * mf::BK) && t * sp <= cus; ++sp)
       if (usable(sp) && t * sp > most) {
         most = t * sp;
         best = {sp, d[0], d[1], 3};
       }
   }
-  return best;
+  return 4 * most >= 5 * whole ? best : none;
 }
 
 int splitk_splits(int epi, int M, int N, int K) { return splitk_plan(epi, M, N, K).splits; }
@@ -2068,7 +2081,7 @@ static hipError_t launch_splitk(int M, int N, int K, const void *A, const void *
   }
   const int MT = (M + 32 * WTA - 1) / (32 * WTA), NT = (N + 64 * WT - 1) / (64 * WT);
   hipLaunchKernelGGL(kern, dim3(MT * NT * sp), dim3(512), lds, s, M, N, K, (const bf16 *)A, (const bf16 *)Wt, part,
-                     MT, NT, ks, group_rows(MT, NT, K));
+                     MT, NT, ks, group_rows(NT, kSplitGroup));
   return hipGetLastError();
 }
 
