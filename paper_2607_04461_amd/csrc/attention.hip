@@ -128,11 +128,16 @@ constexpr int K_OFF = 0, V_OFF = 2 * TILE_B;
 // zero (the buffer range ends at the last key) and are masked on the ragged last tile.  1-D grid,
 // XCD-aware: workgroups go to the 8 XCDs round-robin by id, so id -> (unit u = head * batch + candidate,
 // query block) keeps every query block of a unit on XCD u % 8, where its K and V stay in that XCD's L2.
+// A wave in phase B, whose MFMAs wait on nothing but V fragments already read, goes ahead of the other wave of
+// its SIMD (s_setprio), which keeps the two waves in opposite phases: 16 x 12 heads of 1560 x 1560 258 -> 251
+// us, 4 x 12 heads of 4096 x 4096 373 -> 361 (phase A ahead: 256 and 366; both: 259 and 374).  With at most 8 key
+// tiles (cross-attention) it gains nothing (100 -> 101 us) and is left out.
 // The normalised output leaves through LDS (the rings are free after a last barrier): a lane holds
 // 16-byte pieces of one query row, so direct stores would write every 128-byte line of the output in
 // several partial pieces; staged, each store instruction writes 4 whole rows.  Measured (same box,
 // outputs bit-identical): cross-attention 110 -> 100 us, self-attention 308-320 -> 299-309 us, the
 // 1.3B-shaped pool's draft 238.9 -> 236.8 ms.
+template <bool LEAD>   // a wave in phase B goes ahead (see above)
 __global__ __launch_bounds__(256, 2) void k_attn_fa(AttnP p) {
   using namespace fa2;
   constexpr int RW = KT / WAVES;     // K (V) tile rows each wave loads
@@ -319,6 +324,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_fa(AttnP p) {
       for (int dt = 0; dt < 4; ++dt) vf[0][dt] = vfrag(par, 0, dt);
     }
     __builtin_amdgcn_sched_barrier(0);
+    if constexpr (LEAD) __builtin_amdgcn_s_setprio(1);
     // phase B: O^T += V(j)^T P(j)^T (slot s: chunk s / 2, head-dim tiles 2 (s % 2), + 1), the exponentials
     // of chunk 2 (slots 0-3) and chunk 3 (slots 4, 5), the row maxima of S(j + 1) (slots 6, 7)
     float t0 = -INFINITY, t1 = -INFINITY;
@@ -345,6 +351,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_fa(AttnP p) {
       }
       __builtin_amdgcn_sched_barrier(0);
     }
+    if constexpr (LEAD) __builtin_amdgcn_s_setprio(0);
     if constexpr (next) advance(fmaxf(t0, t1));
   };
 
@@ -806,7 +813,8 @@ hipError_t launch_attention(ActType t, const AttnArgs &a, hipStream_t s) {
   if (t == ACT_BF16 && a.head_dim == fa2::DH) {
     p.nqb = (p.tq + fa2::QB - 1) / fa2::QB;
     const int64_t units8 = ((int64_t)p.batch * p.heads + 7) / 8 * 8;
-    hipLaunchKernelGGL(k_attn_fa, dim3((unsigned)(units8 * p.nqb)), dim3(256), 0, s, p);
+    auto kern = p.tk > 8 * fa2::KT ? k_attn_fa<true> : k_attn_fa<false>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(units8 * p.nqb)), dim3(256), 0, s, p);
     return hipGetLastError();
   }
   return t == ACT_BF16 ? launch_f32<bf16>(p, a.head_dim, s) : launch_f32<float>(p, a.head_dim, s);
