@@ -1235,31 +1235,35 @@ __global__ __launch_bounds__(256, 1) void k_linear_dma(int M, int N, int K, cons
 // 32 rows x 64 columns per workgroup for layers with at most one such tile per CU, the head with its latent
 // update (EPI_EULER) among them.  Eight waves take the K chunks of 64 in turn, their fragments straight from
 // memory (a lane's 16 bytes of A and W rows are the MFMA operands), one chunk ahead; the sums are added
-// through LDS in wave order.  What the epilogue reads (pixels, residual rows) is read before the sums.  Bound by
+// through LDS in wave order.  What the epilogue reads (pixels, residual rows) is read before the sums.  LN: the A rows are adaLN of fp32 rows,
+// normalised into LDS first (every column tile does it again, for less than a launch costs).  Bound by
 // the chain of loads, which 128x128 tiles stretch over more K tiles and fewer CUs; times at the dispatch.
 namespace nar {
 constexpr int BM = 32, BN = 64, WAVES = 8, LDR = BN + 4;   // LDR: floats of a row of sums
 }
-template <int EPI>
+template <int EPI, int LN>   // LN: 0, or the 16-byte pieces a lane holds of an adaLN row (K <= 64 LN)
 __global__ __launch_bounds__(64 * nar::WAVES, 2) void k_linear_narrow(int M, int N, int K, const bf16 *__restrict__ A,
-                                                               const bf16 *__restrict__ Wt, EpiArgs e) {
+                                                               const bf16 *__restrict__ Wt, EpiArgs e, LnArgs ln) {
   using namespace nar;
   __shared__ __attribute__((aligned(16))) float sums[WAVES][BM][LDR];
   const int tid = threadIdx.x, lane = tid & 63, fr = lane & 15, fq = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int m0 = blockIdx.x * BM, n0 = blockIdx.y * BN;
   // rows past the end and columns past K read as zero
-  const __amdgpu_buffer_rsrc_t rsA = epi::rsrc(A + (int64_t)m0 * K, (uint32_t)min(M - m0, BM) * (uint32_t)K * 2u);
+  const __amdgpu_buffer_rsrc_t rsA = epi::rsrc(LN ? nullptr : A + (int64_t)m0 * K, LN ? 0u : (uint32_t)min(M - m0, BM) * (uint32_t)K * 2u);
   const __amdgpu_buffer_rsrc_t rsW = epi::rsrc(Wt + (int64_t)n0 * K, (uint32_t)min(N - n0, BN) * (uint32_t)K * 2u);
   const int chunks = (K + 63) / 64;
+  bf16 *rows = reinterpret_cast<bf16 *>(sums);   // LN: the operand rows, K + 8 apart (an odd number of 16-byte pieces)
   u32x4 fa[2][2][2], fw[2][4][2];   // [buffer][16 rows][32 columns of K]
   auto load = [&](int ch, int buf) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int k = 64 * ch + 32 * h + 8 * fq;
       const uint32_t kb = k < K ? (uint32_t)k * 2u : epi::OUT_OF_RANGE;
+      if constexpr (LN == 0) {
 #pragma unroll
-      for (int j = 0; j < 2; ++j) fa[buf][j][h] = __builtin_amdgcn_raw_buffer_load_b128(rsA, (uint32_t)((16 * j + fr) * K) * 2u + kb, 0, 0);
+        for (int j = 0; j < 2; ++j) fa[buf][j][h] = __builtin_amdgcn_raw_buffer_load_b128(rsA, (uint32_t)((16 * j + fr) * K) * 2u + kb, 0, 0);
+      }
 #pragma unroll
       for (int i = 0; i < 4; ++i) fw[buf][i][h] = __builtin_amdgcn_raw_buffer_load_b128(rsW, (uint32_t)((16 * i + fr) * K) * 2u + kb, 0, 0);
     }
@@ -1269,17 +1273,64 @@ __global__ __launch_bounds__(64 * nar::WAVES, 2) void k_linear_narrow(int M, int
   for (int i = 0; i < 4; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0, 0, 0, 0};
-  auto mul = [&](int buf) {
+  auto mul = [&](int ch, int buf) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
+    for (int h = 0; h < 2; ++h) {
+      if constexpr (LN != 0) {
+        const int k = 64 * ch + 32 * h;
+        if (k >= K) break;   // K % 32 == 0
+#pragma unroll
+        for (int j = 0; j < 2; ++j) fa[buf][j][h] = *reinterpret_cast<const u32x4 *>(rows + (16 * j + fr) * (K + 8) + k + 8 * fq);
+      }
 #pragma unroll
       for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fw[buf][i][h]),
                                                               __builtin_bit_cast(bf16x8, fa[buf][j][h]), acc[i][j], 0, 0, 0);
+    }
   };
   if (wave < chunks) load(wave, 0);
+  if constexpr (LN != 0) {
+    // the operand is adaLN of the fp32 rows (K <= 1024): a wave takes four rows, 16 lanes each, so that a
+    // row's two sums are four exchanges apiece and not six for every row in turn
+    static_assert(BM * (1024 + 8) * 2 <= sizeof(sums), "the rows fit the sums' LDS");
+    const int nv = K >> 2, l16 = lane & 15, row = 4 * wave + (lane >> 4);
+    const float4 *x = reinterpret_cast<const float4 *>(ln.x + (int64_t)min(m0 + row, M - 1) * K);
+    float4 v[LN];
+    float s = 0.f, q = 0.f;
+#pragma unroll
+    for (int i = 0; i < LN; ++i) v[i] = l16 + 16 * i < nv ? x[l16 + 16 * i] : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int i = 0; i < LN; ++i) s += (v[i].x + v[i].y) + (v[i].z + v[i].w);
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    const float mean = s / (float)K;
+#pragma unroll
+    for (int i = 0; i < LN; ++i)
+      if (l16 + 16 * i < nv) {
+        v[i] = make_float4(v[i].x - mean, v[i].y - mean, v[i].z - mean, v[i].w - mean);
+        q += (v[i].x * v[i].x + v[i].y * v[i].y) + (v[i].z * v[i].z + v[i].w * v[i].w);
+      }
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) q += __shfl_xor(q, o, 64);
+    const float rstd = 1.0f / sqrtf(q / (float)K + ln.eps);
+#pragma unroll
+    for (int i = 0; i < LN; ++i) {
+      const int c = l16 + 16 * i;
+      if (c >= nv) break;
+      float o[4] = {v[i].x * rstd, v[i].y * rstd, v[i].z * rstd, v[i].w * rstd};
+      if (ln.shift) {
+        const float4 sh = reinterpret_cast<const float4 *>(ln.shift)[c], sc = reinterpret_cast<const float4 *>(ln.scale)[c];
+        o[0] = o[0] * (1.0f + sc.x) + sh.x;
+        o[1] = o[1] * (1.0f + sc.y) + sh.y;
+        o[2] = o[2] * (1.0f + sc.z) + sh.z;
+        o[3] = o[3] * (1.0f + sc.w) + sh.w;
+      }
+      *reinterpret_cast<bf16x4 *>(rows + row * (K + 8) + 4 * c) = bf16x4{(bf16)o[0], (bf16)o[1], (bf16)o[2], (bf16)o[3]};
+    }
+    __syncthreads();
+  }
   // EULER with p = 2: a wave takes every eighth pixel row of the tile's 32 tokens.  Other epilogues: a
   // thread's 4 columns of one row.
   const bool pairs = EPI == EPI_EULER && e.p == 2;
@@ -1295,10 +1346,11 @@ __global__ __launch_bounds__(64 * nar::WAVES, 2) void k_linear_narrow(int M, int
   }
   for (int ch = wave; ch < chunks; ch += 2 * WAVES) {
     if (ch + WAVES < chunks) load(ch + WAVES, 1);
-    mul(0);
+    mul(ch, 0);
     if (ch + 2 * WAVES < chunks) load(ch + 2 * WAVES, 0);
-    if (ch + WAVES < chunks) mul(1);
+    if (ch + WAVES < chunks) mul(ch + WAVES, 1);
   }
+  if constexpr (LN != 0) __syncthreads();   // every wave has read the rows
   // acc[i][j]: columns 16 i + 4 fq .. + 3 of row 16 j + fr
 #pragma unroll
   for (int i = 0; i < 4; ++i)
@@ -1504,28 +1556,60 @@ __global__ __launch_bounds__(256) void k_linear_valu(int M, int N, int K, const 
 }
 
 // 16x16 tiles, a thread computing a quarter of K of 1 row x 4 columns straight from memory: no LDS, no
-// barrier.  For the shortest sums, where a launch is little but its load latency.
-template <int EPI>
+// barrier.  For the shortest sums, where a launch is little but its load latency.  LN: the operand is adaLN of
+// fp32 rows, made where it is used.
+template <int EPI, bool LN>
 __global__ __launch_bounds__(256) void k_linear_valu_dot(int M, int N, int K, const float *__restrict__ A,
-                                                         const float *__restrict__ Wt, EpiArgs e) {
+                                                         const float *__restrict__ Wt, EpiArgs e, LnArgs ln) {
   const int tid = threadIdx.x, part = tid & 3;
   const int m = blockIdx.x * 16 + (tid >> 4), n = blockIdx.y * 16 + 4 * ((tid >> 2) & 3);
   const bool live = m < M && n < N;   // N % 4 == 0
+  const int c4 = K / 4;
+  const f32x4u *w = reinterpret_cast<const f32x4u *>(Wt + (int64_t)(live ? n : 0) * K);
   float acc[4] = {};
-  if (live) {
-    const f32x4u *a = reinterpret_cast<const f32x4u *>(A + (int64_t)m * K);
-    const f32x4u *w = reinterpret_cast<const f32x4u *>(Wt + (int64_t)n * K);
-    const int c4 = K / 4;
-#pragma unroll 4
-    for (int c = part; c < c4; c += 4) {
-      const f32x4u x = a[c];
+  auto chunk = [&](int c, f32x4u x) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const f32x4u y = w[j * c4 + c];
+    for (int j = 0; j < 4; ++j) {
+      const f32x4u y = w[j * c4 + c];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) acc[j] = fmaf(x[q], y[q], acc[j]);
-      }
+      for (int q = 0; q < 4; ++q) acc[j] = fmaf(x[q], y[q], acc[j]);
     }
+  };
+  if constexpr (LN != 0) {
+    // the operand is adaLN of the fp32 row (K <= 64), whose quarters the four lanes of an output hold
+    const f32x4u *a = reinterpret_cast<const f32x4u *>(ln.x + (int64_t)min(m, M - 1) * K);
+    f32x4u x[4];
+    float s = 0.f, q2 = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      x[i] = part + 4 * i < c4 ? a[part + 4 * i] : f32x4u{0.f, 0.f, 0.f, 0.f};
+      s += (x[i][0] + x[i][1]) + (x[i][2] + x[i][3]);
+    }
+    s += __shfl_xor(s, 1, 64);
+    s += __shfl_xor(s, 2, 64);
+    const float mean = s / (float)K;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (part + 4 * i < c4) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) x[i][q] -= mean;
+        q2 += (x[i][0] * x[i][0] + x[i][1] * x[i][1]) + (x[i][2] * x[i][2] + x[i][3] * x[i][3]);
+      }
+    q2 += __shfl_xor(q2, 1, 64);
+    q2 += __shfl_xor(q2, 2, 64);
+    const float rstd = 1.0f / sqrtf(q2 / (float)K + ln.eps);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int c = part + 4 * i;
+      if (!live || c >= c4) break;
+      f32x4u y = x[i] * rstd;
+      if (ln.shift) y = y * (1.0f + reinterpret_cast<const f32x4u *>(ln.scale)[c]) + reinterpret_cast<const f32x4u *>(ln.shift)[c];
+      chunk(c, y);
+    }
+  } else if (live) {
+    const f32x4u *a = reinterpret_cast<const f32x4u *>(A + (int64_t)m * K);
+#pragma unroll 4
+    for (int c = part; c < c4; c += 4) chunk(c, a[c]);
   }
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
@@ -1893,7 +1977,7 @@ static hipError_t launch_f32(int M, int N, int K, const float *A, const float *W
 template <int EPI>
 static hipError_t launch_narrow(int M, int N, int K, const void *A, const void *Wt, const EpiArgs &e, hipStream_t s) {
   const dim3 grid((M + nar::BM - 1) / nar::BM, (N + nar::BN - 1) / nar::BN);
-  hipLaunchKernelGGL(k_linear_narrow<EPI>, grid, dim3(64 * nar::WAVES), 0, s, M, N, K, (const bf16 *)A, (const bf16 *)Wt, e);
+  hipLaunchKernelGGL((k_linear_narrow<EPI, 0>), grid, dim3(64 * nar::WAVES), 0, s, M, N, K, (const bf16 *)A, (const bf16 *)Wt, e, LnArgs{});
   return hipGetLastError();
 }
 
@@ -1941,7 +2025,8 @@ static hipError_t launch_epi(ActType t, int M, int N, int K, const void *A, cons
   if (t == ACT_BF16) {
     if constexpr (EPI == EPI_EULER) {
       // the head: its columns are one tile wide, so past one 32x64 tile a CU the 128x128 tile's whole-row loads
-      // stream A better (24960 rows of K = 1536: 28 us, 44 on 32x64 tiles; 58 on 128x128 tiles with four divisions an output)
+      // stream A better (24960 rows of K = 1536: 28 us against 44;
+      // 58 on 128x128 tiles with four divisions an output)
       const bool dma_ok = K % mf::BK == 0 && K >= 2 * mf::BK && N % 8 == 0;
       if (dma_ok && !narrow_fits(M, N, K)) return launch_deep<EPI, 4, 2, 3>(M, N, K, A, Wt, e, s);
       return launch_narrow<EPI>(M, N, K, A, Wt, e, s);
@@ -1956,11 +2041,45 @@ static hipError_t launch_epi(ActType t, int M, int N, int K, const void *A, cons
     case F32_MID: return launch_f32<EPI, 2, 2, 1, 1, 1, 2>(M, N, K, Af, Wf, e, s);
     case F32_SMALL: return launch_f32<EPI, 1, 1, 4, 1, 1, 3>(M, N, K, Af, Wf, e, s);
     case F32_DOT:
-      hipLaunchKernelGGL(k_linear_valu_dot<EPI>, dim3((M + 15) / 16, (N + 15) / 16), dim3(256), 0, s, M, N, K, Af, Wf, e);
+      hipLaunchKernelGGL((k_linear_valu_dot<EPI, false>), dim3((M + 15) / 16, (N + 15) / 16), dim3(256), 0, s, M, N, K, Af, Wf, e,
+                         LnArgs{});
       break;
     case F32_VALU:
       hipLaunchKernelGGL(k_linear_valu<EPI>, dim3((M + 63) / 64, (N + 63) / 64), dim3(256), 0, s, M, N, K, Af, Wf, e);
       break;
+  }
+  return hipGetLastError();
+}
+
+// adaLN rows that the next layer's kernel can make for itself, for less than a launch costs (bf16, 390 rows of 256:
+// 6.4 us against 4.2 for the layer and 3.5 for k_ln_mod; 32 rows of 64 3.6 against 2.1 and 3.0; and a launch
+// less on the host, which such steps wait for): layers that k_linear_narrow takes (rows of at
+// most 1024, whose 32 fit LDS beside nothing else) or, in fp32, k_linear_valu_dot.  A forced tile takes the layer alone.
+bool ln_linear_takes(ActType t, int M, int N, int D) {
+  if (getenv("FLASHBON_LINEAR_TILE")) return false;
+  return t == ACT_BF16 ? D <= 1024 && narrow_fits(M, N, D) : f32_tile(M, N, D, true) == F32_DOT;
+}
+
+template <int EPI>
+static void ln_linear(ActType t, int M, int N, int D, const LnArgs &ln, const void *Wt, const EpiArgs &e, hipStream_t s) {
+  if (t == ACT_BF16) {
+    auto kern = D <= 256 ? k_linear_narrow<EPI, 4> : k_linear_narrow<EPI, 16>;
+    hipLaunchKernelGGL(kern, dim3((M + nar::BM - 1) / nar::BM, (N + nar::BN - 1) / nar::BN), dim3(64 * nar::WAVES), 0, s, M,
+                       N, D, nullptr, (const bf16 *)Wt, e, ln);
+  } else {
+    hipLaunchKernelGGL((k_linear_valu_dot<EPI, true>), dim3((M + 15) / 16, (N + 15) / 16), dim3(256), 0, s, M, N, D, nullptr,
+                       (const float *)Wt, e, ln);
+  }
+}
+
+hipError_t launch_ln_linear(ActType t, int epi, int M, int N, int D, const LnArgs &ln, const void *Wt, const EpiArgs &e,
+                            hipStream_t s) {
+  switch (epi) {
+    case EPI_STORE: ln_linear<EPI_STORE>(t, M, N, D, ln, Wt, e, s); break;
+    case EPI_GELU: ln_linear<EPI_GELU>(t, M, N, D, ln, Wt, e, s); break;
+    case EPI_STORE_F32: ln_linear<EPI_STORE_F32>(t, M, N, D, ln, Wt, e, s); break;
+    case EPI_EULER: ln_linear<EPI_EULER>(t, M, N, D, ln, Wt, e, s); break;
+    default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }

@@ -44,6 +44,16 @@ constexpr size_t kSplitBytes = (size_t)48 << 20;
 int splitk_splits(int epi, int M, int N, int K);
 hipError_t launch_linear_ws(ActType t, int epi, int M, int N, int K, const void *A, const void *Wt, const EpiArgs &e,
                             hipStream_t s, void *ws, size_t ws_bytes);
+// adaLN and the linear layer that reads it in one launch, out = epilogue(LN(x) (1 + scale) + shift) Wt^T) (shift and
+// scale null: plain LN; x fp32 [M][D], rounded to the act type as an operand): STORE, GELU, STORE_F32 and EULER,
+// for layers that ln_linear_takes.  Everything on 16 bytes but EULER's latents.
+struct LnArgs {
+  const float *x = nullptr, *shift = nullptr, *scale = nullptr;
+  float eps = 0.f;
+};
+bool ln_linear_takes(ActType t, int M, int N, int D);
+hipError_t launch_ln_linear(ActType t, int epi, int M, int N, int D, const LnArgs &ln, const void *Wt, const EpiArgs &e,
+                            hipStream_t s);
 // The kernels launch_linear would use for this shape, without launching: returns the number of
 // launches and writes a NUL-terminated description (truncated to len - 1 characters) into buf.
 int describe_linear(ActType t, int epi, int M, int N, int K, char *buf, int len);

@@ -475,6 +475,20 @@ static flashbon_status run_step(Model *m, const flashbon_step_args *a, bool draf
     return FLASHBON_OK;
   };
   flashbon_status st;
+  // adaLN (or plain LN) of the stream x and the linear layer that reads it: one launch where the layer's kernel
+  // can make the rows for itself, unless the NORM site is timed, which counts the launch of its own
+  auto ln_lin = [&](const float *x, const float *shift, const float *scale, const char *ln_what, int site, int epi, int N,
+                    const void *W, const EpiArgs &e, const char *what) -> flashbon_status {
+    if (!(tmask & (1u << FLASHBON_SITE_NORM)) && ln_linear_takes(act, (int)M, N, D)) {
+      LnArgs ln;
+      ln.x = x; ln.shift = shift; ln.scale = scale; ln.eps = c.ln_eps;
+      HIPCHK(timed(m, tmask, site, s, [&] { return launch_ln_linear(act, epi, (int)M, N, D, ln, W, e, s); }), what);
+      return FLASHBON_OK;
+    }
+    HIPCHK(timed(m, tmask, FLASHBON_SITE_NORM, s, [&] { return launch_ln_mod(act, (int)M, D, c.ln_eps, x, shift, scale, B.a, s); }), ln_what);
+    HIPCHK(timed(m, tmask, site, s, [&] { return lin(act, epi, (int)M, N, D, B.a, W, e, s); }), what);
+    return FLASHBON_OK;
+  };
 
   // patch embedding, unless the first non-skipped block is a proxy (its input is then never read)
   bool embed_live = true;
@@ -525,10 +539,9 @@ static flashbon_status run_step(Model *m, const flashbon_step_args *a, bool draf
     if (residual)
       HIPCHK(hipMemcpyAsync(a->cache + ((int64_t)l * 3 + tr.slot) * MD, B.h, MD * 4, hipMemcpyDeviceToDevice, s),
              "block input to cache");
-    HIPCHK(timed(m, tmask, FLASHBON_SITE_NORM, s, [&] { return launch_ln_mod(act, (int)M, D, c.ln_eps, hcur, mod + 0 * D, mod + 1 * D, B.a, s); }), "adaLN 1");
     {
       EpiArgs e; e.out = B.qkv; e.ldo = 3 * D; e.bias = Bp(b.bqkv);
-      HIPCHK(timed(m, tmask, FLASHBON_SITE_QKV, s, [&] { return lin(act, EPI_STORE, (int)M, 3 * D, D, B.a, Wp(b.wqkv), e, s); }), "qkv projection");
+      if ((st = ln_lin(hcur, mod + 0 * D, mod + 1 * D, "adaLN 1", FLASHBON_SITE_QKV, EPI_STORE, 3 * D, Wp(b.wqkv), e, "qkv projection")) != FLASHBON_OK) return st;
     }
     if (c.qk_norm_rope) {
       void *kp = (char *)B.qkv + (size_t)D * asz;
@@ -549,10 +562,9 @@ static flashbon_status run_step(Model *m, const flashbon_step_args *a, bool draf
       HIPCHK(timed(m, tmask, FLASHBON_SITE_OUT, s, [&] { return lin(act, EPI_RESIDUAL, (int)M, D, D, B.o, Wp(b.wo), e, s); }), "self-attn out projection");
       hcur = B.h;
     }
-    HIPCHK(timed(m, tmask, FLASHBON_SITE_NORM, s, [&] { return launch_ln_mod(act, (int)M, D, c.ln_eps, B.h, nullptr, nullptr, B.a, s); }), "cross LN");
     {
       EpiArgs e; e.out = B.qkv; e.ldo = D; e.bias = Bp(b.bqc);
-      HIPCHK(timed(m, tmask, FLASHBON_SITE_CROSS_Q, s, [&] { return lin(act, EPI_STORE, (int)M, D, D, B.a, Wp(b.wqc), e, s); }), "cross q projection");
+      if ((st = ln_lin(B.h, nullptr, nullptr, "cross LN", FLASHBON_SITE_CROSS_Q, EPI_STORE, D, Wp(b.wqc), e, "cross q projection")) != FLASHBON_OK) return st;
     }
     if (c.qk_norm_rope)
       HIPCHK(timed(m, tmask, FLASHBON_SITE_NORM, s, [&] { return launch_qk_norm(act, (int)M, D, dh, B.qkv, nullptr, D, Bp(b.nqc), nullptr, c.ln_eps, nullptr, T, s); }), "cross q RMSNorm");
@@ -570,10 +582,9 @@ static flashbon_status run_step(Model *m, const flashbon_step_args *a, bool draf
       EpiArgs e; e.out = B.h; e.ldo = D; e.bias = Bp(b.boc);
       HIPCHK(timed(m, tmask, FLASHBON_SITE_OUT_CROSS, s, [&] { return lin(act, EPI_RESIDUAL, (int)M, D, D, B.o, Wp(b.woc), e, s); }), "cross out projection");
     }
-    HIPCHK(timed(m, tmask, FLASHBON_SITE_NORM, s, [&] { return launch_ln_mod(act, (int)M, D, c.ln_eps, B.h, mod + 3 * D, mod + 4 * D, B.a, s); }), "adaLN 2");
     {
       EpiArgs e; e.out = B.u; e.ldo = F; e.bias = Bp(b.b1);
-      HIPCHK(timed(m, tmask, FLASHBON_SITE_MLP_UP, s, [&] { return lin(act, EPI_GELU, (int)M, F, D, B.a, Wp(b.w1), e, s); }), "mlp up");
+      if ((st = ln_lin(B.h, mod + 3 * D, mod + 4 * D, "adaLN 2", FLASHBON_SITE_MLP_UP, EPI_GELU, F, Wp(b.w1), e, "mlp up")) != FLASHBON_OK) return st;
     }
     {
       EpiArgs e; e.out = B.h; e.ldo = D; e.bias = Bp(b.b2); e.gate = mod + 5 * D;
@@ -592,7 +603,6 @@ static flashbon_status run_step(Model *m, const flashbon_step_args *a, bool draf
   }
 
   // head + unpatchify + Euler update of the latents (or the stochastic update of Eq. 20)
-  HIPCHK(timed(m, tmask, FLASHBON_SITE_NORM, s, [&] { return launch_ln_mod(act, (int)M, D, c.ln_eps, hcur, B.hmod, B.hmod + D, B.a, s); }), "head adaLN");
   if (stochastic || guided) {
     if (!stochastic) {                      // Euler update through the same kernel: no drift term, no noise
       sde = SdeArgs{};
@@ -600,7 +610,7 @@ static flashbon_status run_step(Model *m, const flashbon_step_args *a, bool draf
     }
     EpiArgs e;
     e.out = B.vtok; e.ldo = P; e.bias = Bp(m->lay.head_b);
-    HIPCHK(timed(m, tmask, FLASHBON_SITE_HEAD, s, [&] { return lin(act, EPI_STORE_F32, (int)M, P, D, B.a, Wp(m->lay.head_w), e, s); }), "head");
+    if ((st = ln_lin(hcur, B.hmod, B.hmod + D, "head adaLN", FLASHBON_SITE_HEAD, EPI_STORE_F32, P, Wp(m->lay.head_w), e, "head")) != FLASHBON_OK) return st;
     HIPCHK(timed(m, tmask, FLASHBON_SITE_HEAD, s, [&] { return launch_head_update(a->n, m->C, a->latent_h, a->latent_w, p, B.vtok, guided, a->cfg_scale, a->latents, sde, a->preview, a->t_cur, s); }),
            "unpatchify + guidance + update");
   } else {
@@ -608,7 +618,7 @@ static flashbon_status run_step(Model *m, const flashbon_step_args *a, bool draf
     e.bias = Bp(m->lay.head_b); e.z = a->latents; e.dt = a->t_next - a->t_cur;
     e.preview = a->preview; e.t_cur = a->t_cur;
     e.C = m->C; e.H = a->latent_h; e.W = a->latent_w; e.p = p; e.T = T;
-    HIPCHK(timed(m, tmask, FLASHBON_SITE_HEAD, s, [&] { return lin(act, EPI_EULER, (int)M, P, D, B.a, Wp(m->lay.head_w), e, s); }), "head + Euler");
+    if ((st = ln_lin(hcur, B.hmod, B.hmod + D, "head adaLN", FLASHBON_SITE_HEAD, EPI_EULER, P, Wp(m->lay.head_w), e, "head + Euler")) != FLASHBON_OK) return st;
   }
 
   // ---------------------------------------------------------------- commit host state
