@@ -1810,26 +1810,30 @@ static hipError_t launch_mfma(int M, int N, int K, const void *A, const void *Wt
   return hipGetLastError();
 }
 
-// Row blocks per tile group of the linear kernels' order (see mf::tile_of).  Narrow outputs (at most
-// 8 column tiles) take groups of 1, so an XCD runs every column tile of a row block together and each
-// A row block (3.4 MB at K = 8960) is fetched once rather than again in a later round; up to 24 column
-// tiles groups of 8 (the 32 tiles an XCD runs at once then span 8 row blocks x 4 column tiles), wider
-// outputs groups of 6.  Swept in the 1.3B-shaped draft (M = 24960) on the 8-wave kernel: MLP down
-// (N = 1536, K = 8960) best at 1 (61.2 ms per draft against 65.0 at 8), the K = 1536, N = 1536
-// projections at 1 (about 1% ahead of 4), QKV (18 column tiles) at 8, MLP up (35) at 6 (55.8 against
-// 56.5 ms at 8).  The order does not change any output.  FLASHBON_LINEAR_GROUP (tuning): a fixed
-// group height.
+// Row blocks per tile group of the linear kernels' order (see mf::tile_of); the order does not change any output.
+// Narrow outputs (at most 8 column tiles) take groups of 1, so an XCD runs every column tile of a row block
+// together and each A row block (3.4 MB at K = 8960) is fetched once rather than again in a later round: MLP down
+// of the 1.3B-shaped draft (M = 24960, N = 1536, K = 8960) 61.2 ms per draft against 65.0 at 8, the K = 1536,
+// N = 1536 projections about 1% ahead of 4; MLP up (35 column tiles) 55.8 ms at 6 against 56.5 at 8.
+// FLASHBON_LINEAR_GROUP (tuning): a fixed group height.
+// Over M = 2500 .. 24960 at K = 1536, 5120 and 13824: up to 24 column tiles at K = 1536 5 rather than 8
+// (18 tiles: M = 8000 94.9 us against 97.6, 12000 133.8 against 136.5, 24960 270.9 against 275.4); beyond 24 at
+// K >= 4096 4 rather than 6 (60 tiles: M = 12000 1392 us against 1442, 16384 1891 against 1922; 54 tiles: 16384 1723
+// against 1766; 4096 and 8192 within 1% of each other).  20 tiles at K = 5120 keep 8: 3 is faster at M = 16384 (704 us
+// against 760) and slower at 8192 (371 against 354).
+//
 // Launches of one round have orders of their own, all their tiles being at work at once: groups of 5 row blocks
 // for the deep-ring tile ((1560, 1536, 1536) 13.9 us, 14.5 at 8 and 15.1 at 1; (3120, 1536, 8960) 77.0, 77.4 and
 // 77.7), groups of 3 for split-K ((1560, 1536, 8960) 49.0 us, 49.7 at 1 and 49.2 at 8; (500, 5120, 13824) 71.9, 83.2
 // and 69.7; (512, 1536, 4096) 17.3, 17.3 and 19.8).
 constexpr int kDeepGroup = 5, kSplitGroup = 3;
-static int group_rows(int NT, int otherwise = 0) {
+static int group_rows(int NT, int K, int otherwise = 0) {
   const char *force = getenv("FLASHBON_LINEAR_GROUP");
   if (force && atoi(force) > 0) return atoi(force);
   if (otherwise) return otherwise;
   if (NT <= 8) return 1;
-  return NT <= 24 ? mf::GROUP_M : 6;
+  if (K >= 4096) return NT <= 24 ? mf::GROUP_M : 4;
+  return NT <= 24 ? 5 : 6;
 }
 
 // The 4-wave kernel over mb row blocks, `tall` of them 32 WTA rows high, the rest 32 (WTA - 1).
@@ -1847,7 +1851,7 @@ static hipError_t launch_dma(int M, int N, int K, const void *A, const void *Wt,
   }
   const int NT = (N + 255) / 256;
   hipLaunchKernelGGL(kern, dim3(mb * NT), dim3(256), lds, s, M, N, K, (const bf16 *)A, (const bf16 *)Wt, e,
-                     mb, NT, tall, group_rows(NT));
+                     mb, NT, tall, group_rows(NT, K));
   return hipGetLastError();
 }
 
@@ -1872,7 +1876,7 @@ static hipError_t launch_dma8(int M, int N, int K, const void *A, const void *Wt
   }
   const int NT = (N + 255) / 256;
   hipLaunchKernelGGL(kern, dim3(mb * NT), dim3(512), lds, s, M, N, K, (const bf16 *)A, (const bf16 *)Wt, e, mb, NT,
-                     tall, group_rows(NT));
+                     tall, group_rows(NT, K));
   return hipGetLastError();
 }
 
@@ -1889,7 +1893,7 @@ static hipError_t launch_deep(int M, int N, int K, const void *A, const void *Wt
   }
   const int MT = (M + 32 * WTA - 1) / (32 * WTA), NT = (N + 64 * WT - 1) / (64 * WT);
   hipLaunchKernelGGL(kern, dim3(MT * NT), dim3(512), lds, s, M, N, K, (const bf16 *)A, (const bf16 *)Wt, e, MT, NT,
-                     group_rows(NT, kDeepGroup));
+                     group_rows(NT, K, kDeepGroup));
   return hipGetLastError();
 }
 
@@ -2200,7 +2204,7 @@ static hipError_t launch_splitk(int M, int N, int K, const void *A, const void *
   }
   const int MT = (M + 32 * WTA - 1) / (32 * WTA), NT = (N + 64 * WT - 1) / (64 * WT);
   hipLaunchKernelGGL(kern, dim3(MT * NT * sp), dim3(512), lds, s, M, N, K, (const bf16 *)A, (const bf16 *)Wt, part,
-                     MT, NT, ks, group_rows(NT, kSplitGroup));
+                     MT, NT, ks, group_rows(NT, K, kSplitGroup));
   return hipGetLastError();
 }
 
