@@ -167,7 +167,14 @@ def _u8(mask: Optional[Sequence[int]], n: int):
     a = np.ascontiguousarray(np.asarray(mask, dtype=np.uint8))
     if a.shape != (n,):
         raise ValueError(f"mask must have shape ({n},)")
-    return a, a.ctypes.data_as(ctypes.POINTER(ctypes.c_uint8))
+    c = _c_array(ctypes.c_uint8, a)
+    return c, c
+
+
+def _c_array(ctype, a: np.ndarray):
+    """The values of a contiguous array as a ctypes array, which pointer arguments and fields take as it is
+    (ndarray.ctypes.data_as costs several times as much, on every step)."""
+    return (ctype * a.size).from_buffer_copy(a)
 
 
 def make_config(shape, dtype: int, max_n: int, max_tokens: int, max_text_len: int, max_cond: int) -> ModelConfig:
@@ -225,7 +232,8 @@ def _nbytes(t) -> int:
     return int(t.numel()) * int(t.element_size())
 
 
-def _check_tensor(name: str, t, *, dtype=None, ndim=None, require_device: bool = True) -> None:
+def _check_tensor(name: str, t, *, dtype=None, ndim=None, require_device: bool = True, device: Optional[int] = None) -> None:
+    """``device``: the current device's index, where the caller has it."""
     import torch
     if not isinstance(t, torch.Tensor):
         raise ValueError(f"{name} must be a torch tensor")
@@ -238,9 +246,10 @@ def _check_tensor(name: str, t, *, dtype=None, ndim=None, require_device: bool =
     if require_device:
         if not t.is_cuda:
             raise ValueError(f"{name} must be on the current device (a GPU), got {t.device}")
-        if t.device.index != torch.cuda.current_device():
-            raise ValueError(f"{name} must be on the current device (cuda:{torch.cuda.current_device()}), "
-                             f"got {t.device}")
+        if device is None:
+            device = torch.cuda.current_device()
+        if t.device.index != device:
+            raise ValueError(f"{name} must be on the current device (cuda:{device}), got {t.device}")
 
 
 def validate_step(cfg: ModelConfig, latents, text, text_kv, *, draft: bool, guided: bool = False,
@@ -251,15 +260,16 @@ def validate_step(cfg: ModelConfig, latents, text, text_kv, *, draft: bool, guid
     ``require_device=False`` skips only the device check (host-only tests of the other checks)."""
     import torch
     f32 = torch.float32
-    _check_tensor("latents", latents, dtype=f32, ndim=4, require_device=require_device)
+    device = torch.cuda.current_device() if require_device and isinstance(latents, torch.Tensor) and latents.is_cuda else None
+    _check_tensor("latents", latents, dtype=f32, ndim=4, require_device=require_device, device=device)
     n, C, H, W = (int(x) for x in latents.shape)
     if C != cfg.latent_channels:
         raise ValueError(f"latents have {C} channels, the model {cfg.latent_channels}")
-    _check_tensor("text", text, dtype=f32, ndim=3, require_device=require_device)
+    _check_tensor("text", text, dtype=f32, ndim=3, require_device=require_device, device=device)
     n_cond, text_len, text_dim = (int(x) for x in text.shape)
     if text_dim != cfg.text_dim:
         raise ValueError(f"text tokens are {text_dim} wide, the model takes {cfg.text_dim}")
-    _check_tensor("text_kv", text_kv, require_device=require_device)
+    _check_tensor("text_kv", text_kv, require_device=require_device, device=device)
     need = text_kv_nbytes(cfg, n_cond, text_len)
     if _nbytes(text_kv) < need:
         raise ValueError(f"text_kv holds {_nbytes(text_kv)} bytes, needs {need}")
@@ -269,7 +279,7 @@ def validate_step(cfg: ModelConfig, latents, text, text_kv, *, draft: bool, guid
     if draft:
         if cache is None:
             raise ValueError("a draft step needs the activation cache")
-        _check_tensor("cache", cache, dtype=f32, require_device=require_device)
+        _check_tensor("cache", cache, dtype=f32, require_device=require_device, device=device)
         need = cache_nbytes(cfg, rows, tokens)
         if _nbytes(cache) < need:
             raise ValueError(f"cache holds {_nbytes(cache)} bytes, needs {need} for {rows} rows x {tokens} tokens")
@@ -278,12 +288,12 @@ def validate_step(cfg: ModelConfig, latents, text, text_kv, *, draft: bool, guid
     if trace is not None and len(trace) != cfg.num_blocks:
         raise ValueError(f"trace must hold {cfg.num_blocks} entries")
     if hidden_dump is not None:
-        _check_tensor("hidden_dump", hidden_dump, dtype=f32, require_device=require_device)
+        _check_tensor("hidden_dump", hidden_dump, dtype=f32, require_device=require_device, device=device)
         need = (cfg.num_blocks + 1) * rows * tokens * cfg.hidden
         if int(hidden_dump.numel()) < need:
             raise ValueError(f"hidden_dump holds {int(hidden_dump.numel())} floats, needs {need}")
     if preview is not None:
-        _check_tensor("preview", preview, dtype=f32, ndim=4, require_device=require_device)
+        _check_tensor("preview", preview, dtype=f32, ndim=4, require_device=require_device, device=device)
         if tuple(preview.shape) != tuple(latents.shape):
             raise ValueError(f"preview must have the latents' shape {tuple(latents.shape)}")
         a0, a1 = latents.data_ptr(), latents.data_ptr() + _nbytes(latents)
@@ -342,7 +352,7 @@ def step_args(latents, t_cur, t_next, text, cond_index, text_kv, text_kv_valid, 
     a.t_cur, a.t_next = float(t_cur), float(t_next)
     a.text = _ptr(text)
     a.n_cond, a.text_len = n_cond, text_len
-    a.cond_index = cond.ctypes.data_as(ctypes.POINTER(ctypes.c_int32))
+    cond = a.cond_index = _c_array(ctypes.c_int32, cond)
     a.text_kv = _ptr(text_kv)
     a.text_kv_valid = ctypes.pointer(text_kv_valid)
     a.skip, a.proxy = skp, pxp
@@ -357,7 +367,7 @@ def step_args(latents, t_cur, t_next, text, cond_index, text_kv, text_kv_valid, 
         if unc.shape != (n,):
             raise ValueError(f"uncond_index must have shape ({n},)")
         a.cfg, a.cfg_scale = 1, float(cfg[0])
-        a.uncond_index = unc.ctypes.data_as(ctypes.POINTER(ctypes.c_int32))
+        unc = a.uncond_index = _c_array(ctypes.c_int32, unc)
     a.stream = _stream(stream)
     if sde is not None:
         a.sde_a, a.sde_seed, a.sde_step = float(sde[0]), int(sde[1]), int(sde[2])
