@@ -276,7 +276,7 @@ enum {
   FLASHBON_SITE_OUT_CROSS = 5,  /* cross-attention output projection      */
   FLASHBON_SITE_MLP_UP = 6,     /* MLP up projection + GELU               */
   FLASHBON_SITE_MLP_DOWN = 7,   /* MLP down projection + gate + residual + cache store */
-  FLASHBON_SITE_NORM = 8,       /* the three adaLN / LN launches of a block and the head's */
+  FLASHBON_SITE_NORM = 8,       /* the three adaLN / LN launches of a block and the head's, q/k normalisation */
   FLASHBON_SITE_PROXY = 9,      /* activation proxy                       */
   FLASHBON_SITE_EMBED = 10,     /* patchify + patch embedding             */
   FLASHBON_SITE_HEAD = 11,      /* head projection + unpatchify + Euler   */
@@ -288,7 +288,9 @@ enum {
 /* Enable device timing of the sites in `site_mask` for later calls on this model: the library then
  * records a HIP event pair on the step's stream around every launch at those sites (a few
  * microseconds of host time per launch; 0 disables).  Accumulated results are read, and reset, by
- * flashbon_read_timing. */
+ * flashbon_read_timing.  Timing changes no output.  It changes the launches in one place: small layers make
+ * the adaLN of their rows inside the layer's own launch, and run it as a launch of its own, with the same
+ * values, while FLASHBON_SITE_NORM is timed. */
 flashbon_status flashbon_set_timing(flashbon_model *model, uint32_t site_mask);
 
 /* Synchronise on the recorded events and return, for one site, the summed device time (ms) and the

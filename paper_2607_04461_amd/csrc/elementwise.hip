@@ -42,8 +42,7 @@ __global__ __launch_bounds__(256) void k_ln_mod(int M, int D, float eps, const f
   for (int i = 0; i < NV; ++i) {
     int c = lane + i * 64;
     if (c < nv) {
-      float a = v[i].x - mean, b = v[i].y - mean, cc = v[i].z - mean, d = v[i].w - mean;
-      q += (a * a + b * b) + (cc * cc + d * d);
+      q += sum_sq4(v[i].x - mean, v[i].y - mean, v[i].z - mean, v[i].w - mean);
     }
   }
   const float rstd = 1.0f / sqrtf(wave_sum(q) / (float)D + eps);
@@ -57,10 +56,10 @@ __global__ __launch_bounds__(256) void k_ln_mod(int M, int D, float eps, const f
       if (shift) {
         float4 sh = reinterpret_cast<const float4 *>(shift)[c];
         float4 sc = reinterpret_cast<const float4 *>(scale)[c];
-        r[0] = r[0] * (1.0f + sc.x) + sh.x;
-        r[1] = r[1] * (1.0f + sc.y) + sh.y;
-        r[2] = r[2] * (1.0f + sc.z) + sh.z;
-        r[3] = r[3] * (1.0f + sc.w) + sh.w;
+        r[0] = fmaf(r[0], 1.0f + sc.x, sh.x);
+        r[1] = fmaf(r[1], 1.0f + sc.y, sh.y);
+        r[2] = fmaf(r[2], 1.0f + sc.z, sh.z);
+        r[3] = fmaf(r[3], 1.0f + sc.w, sh.w);
       }
       if constexpr (sizeof(T) == 4) {
         reinterpret_cast<float4 *>(orow)[c] = make_float4(r[0], r[1], r[2], r[3]);

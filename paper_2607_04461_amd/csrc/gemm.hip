@@ -1293,28 +1293,31 @@ __global__ __launch_bounds__(64 * nar::WAVES, 2) void k_linear_narrow(int M, int
   if (wave < chunks) load(wave, 0);
   if constexpr (LN != 0) {
     // the operand is adaLN of the fp32 rows (K <= 1024): a wave takes four rows, 16 lanes each, so that a
-    // row's two sums are four exchanges apiece and not six for every row in turn
+    // row's two sums are four exchanges apiece and not six for every row in turn.  Lane l stands for lanes l, l + 16,
+    // l + 32 and l + 48 of k_ln_mod's row and adds in its order: the rows are the same to the bit.
     static_assert(BM * (1024 + 8) * 2 <= sizeof(sums), "the rows fit the sums' LDS");
     const int nv = K >> 2, l16 = lane & 15, row = 4 * wave + (lane >> 4);
     const float4 *x = reinterpret_cast<const float4 *>(ln.x + (int64_t)min(m0 + row, M - 1) * K);
     float4 v[LN];
-    float s = 0.f, q = 0.f;
+    float s[4] = {}, q[4] = {};
+    auto row_sum = [](const float (&p)[4]) {
+      float t = (p[0] + p[2]) + (p[1] + p[3]);
+#pragma unroll
+      for (int o = 8; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
+      return t;
+    };
 #pragma unroll
     for (int i = 0; i < LN; ++i) v[i] = l16 + 16 * i < nv ? x[l16 + 16 * i] : make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-    for (int i = 0; i < LN; ++i) s += (v[i].x + v[i].y) + (v[i].z + v[i].w);
-#pragma unroll
-    for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-    const float mean = s / (float)K;
+    for (int i = 0; i < LN; ++i) s[i & 3] += (v[i].x + v[i].y) + (v[i].z + v[i].w);
+    const float mean = row_sum(s) / (float)K;
 #pragma unroll
     for (int i = 0; i < LN; ++i)
       if (l16 + 16 * i < nv) {
         v[i] = make_float4(v[i].x - mean, v[i].y - mean, v[i].z - mean, v[i].w - mean);
-        q += (v[i].x * v[i].x + v[i].y * v[i].y) + (v[i].z * v[i].z + v[i].w * v[i].w);
+        q[i & 3] += sum_sq4(v[i].x, v[i].y, v[i].z, v[i].w);
       }
-#pragma unroll
-    for (int o = 8; o > 0; o >>= 1) q += __shfl_xor(q, o, 64);
-    const float rstd = 1.0f / sqrtf(q / (float)K + ln.eps);
+    const float rstd = 1.0f / sqrtf(row_sum(q) / (float)K + ln.eps);
 #pragma unroll
     for (int i = 0; i < LN; ++i) {
       const int c = l16 + 16 * i;
@@ -1322,10 +1325,10 @@ __global__ __launch_bounds__(64 * nar::WAVES, 2) void k_linear_narrow(int M, int
       float o[4] = {v[i].x * rstd, v[i].y * rstd, v[i].z * rstd, v[i].w * rstd};
       if (ln.shift) {
         const float4 sh = reinterpret_cast<const float4 *>(ln.shift)[c], sc = reinterpret_cast<const float4 *>(ln.scale)[c];
-        o[0] = o[0] * (1.0f + sc.x) + sh.x;
-        o[1] = o[1] * (1.0f + sc.y) + sh.y;
-        o[2] = o[2] * (1.0f + sc.z) + sh.z;
-        o[3] = o[3] * (1.0f + sc.w) + sh.w;
+        o[0] = fmaf(o[0], 1.0f + sc.x, sh.x);
+        o[1] = fmaf(o[1], 1.0f + sc.y, sh.y);
+        o[2] = fmaf(o[2], 1.0f + sc.z, sh.z);
+        o[3] = fmaf(o[3], 1.0f + sc.w, sh.w);
       }
       *reinterpret_cast<bf16x4 *>(rows + row * (K + 8) + 4 * c) = bf16x4{(bf16)o[0], (bf16)o[1], (bf16)o[2], (bf16)o[3]};
     }
@@ -1576,34 +1579,40 @@ __global__ __launch_bounds__(256) void k_linear_valu_dot(int M, int N, int K, co
     }
   };
   if constexpr (LN != 0) {
-    // the operand is adaLN of the fp32 row (K <= 64), whose quarters the four lanes of an output hold
+    // the operand is adaLN of the fp32 row (K <= 64), whose quarters the four lanes of an output hold: piece c of
+    // the row belongs to lane c of k_ln_mod, which adds c ^ 8, c ^ 4, c ^ 2 and c ^ 1 in turn
     const f32x4u *a = reinterpret_cast<const f32x4u *>(ln.x + (int64_t)min(m, M - 1) * K);
     f32x4u x[4];
-    float s = 0.f, q2 = 0.f;
+    float s[4], q2[4] = {};
+    auto row_sum = [](const float (&t)[4]) {
+      float u = (t[0] + t[2]) + (t[1] + t[3]);
+      u += __shfl_xor(u, 2, 64);
+      return u + __shfl_xor(u, 1, 64);
+    };
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       x[i] = part + 4 * i < c4 ? a[part + 4 * i] : f32x4u{0.f, 0.f, 0.f, 0.f};
-      s += (x[i][0] + x[i][1]) + (x[i][2] + x[i][3]);
+      s[i] = (x[i][0] + x[i][1]) + (x[i][2] + x[i][3]);
     }
-    s += __shfl_xor(s, 1, 64);
-    s += __shfl_xor(s, 2, 64);
-    const float mean = s / (float)K;
+    const float mean = row_sum(s) / (float)K;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
       if (part + 4 * i < c4) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) x[i][q] -= mean;
-        q2 += (x[i][0] * x[i][0] + x[i][1] * x[i][1]) + (x[i][2] * x[i][2] + x[i][3] * x[i][3]);
+        q2[i] = sum_sq4(x[i][0], x[i][1], x[i][2], x[i][3]);
       }
-    q2 += __shfl_xor(q2, 1, 64);
-    q2 += __shfl_xor(q2, 2, 64);
-    const float rstd = 1.0f / sqrtf(q2 / (float)K + ln.eps);
+    const float rstd = 1.0f / sqrtf(row_sum(q2) / (float)K + ln.eps);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int c = part + 4 * i;
       if (!live || c >= c4) break;
       f32x4u y = x[i] * rstd;
-      if (ln.shift) y = y * (1.0f + reinterpret_cast<const f32x4u *>(ln.scale)[c]) + reinterpret_cast<const f32x4u *>(ln.shift)[c];
+      if (ln.shift) {
+        const f32x4u sc = reinterpret_cast<const f32x4u *>(ln.scale)[c], sh = reinterpret_cast<const f32x4u *>(ln.shift)[c];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) y[q] = fmaf(y[q], 1.0f + sc[q], sh[q]);
+      }
       chunk(c, y);
     }
   } else if (live) {
