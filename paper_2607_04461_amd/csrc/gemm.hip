@@ -53,12 +53,15 @@ __device__ __forceinline__ void euler1(const EpiArgs &e, int64_t zi, float v) {
   if (e.preview) e.preview[zi] = z0 - e.t_cur * v;
   e.z[zi] = z0 + e.dt * v;
 }
-// two pixels side by side
+typedef float f32x2u __attribute__((ext_vector_type(2), aligned(4)));
+// two pixels side by side, a and b before the update
+__device__ __forceinline__ void euler2_from(const EpiArgs &e, int64_t zi, float a, float b, float v0, float v1) {
+  if (e.preview) *reinterpret_cast<f32x2u *>(e.preview + zi) = f32x2u{a - e.t_cur * v0, b - e.t_cur * v1};
+  *reinterpret_cast<f32x2u *>(e.z + zi) = f32x2u{a + e.dt * v0, b + e.dt * v1};
+}
 __device__ __forceinline__ void euler2(const EpiArgs &e, int64_t zi, float v0, float v1) {
-  typedef float f32x2u __attribute__((ext_vector_type(2), aligned(4)));
   const f32x2u z0 = *reinterpret_cast<const f32x2u *>(e.z + zi);
-  if (e.preview) *reinterpret_cast<f32x2u *>(e.preview + zi) = f32x2u{z0[0] - e.t_cur * v0, z0[1] - e.t_cur * v1};
-  *reinterpret_cast<f32x2u *>(e.z + zi) = f32x2u{z0[0] + e.dt * v0, z0[1] + e.dt * v1};
+  euler2_from(e, zi, z0[0], z0[1], v0, v1);
 }
 
 template <int EPI, typename TO>
@@ -92,7 +95,8 @@ __device__ __forceinline__ void epilogue4(const EpiArgs &e, int m, int n, float 
     else h = *reinterpret_cast<const float4 *>(e.res_in ? e.res_in + (int64_t)m * e.ldo + n : o);
     if (e.gate) {
       float4 g = *reinterpret_cast<const float4 *>(e.gate + n);
-      h.x += g.x * v[0]; h.y += g.y * v[1]; h.z += g.z * v[2]; h.w += g.w * v[3];
+      // one rounding, as the MFMA tiles' epilogues have it (the compiler does not fuse across the branch)
+      h = make_float4(fmaf(g.x, v[0], h.x), fmaf(g.y, v[1], h.y), fmaf(g.z, v[2], h.z), fmaf(g.w, v[3], h.w));
     } else {
       h.x += v[0]; h.y += v[1]; h.z += v[2]; h.w += v[3];
     }
@@ -1233,69 +1237,76 @@ __global__ __launch_bounds__(256, 1) void k_linear_dma(int M, int N, int K, cons
 }
 // ------------------------------------------------------------------------- few output tiles, bf16
 // 32 rows x 64 columns per workgroup for layers with at most one such tile per CU, the head with its latent
-// update (EPI_EULER) among them.  Eight waves take the K chunks of 64 in turn, their fragments straight from
-// memory (a lane's 16 bytes of A and W rows are the MFMA operands), one chunk ahead; the sums are added
-// through LDS in wave order.  What the epilogue reads (pixels, residual rows) is read before the sums.  LN: the A rows are adaLN of fp32 rows,
-// normalised into LDS first (every column tile does it again, for less than a launch costs).  Bound by
-// the chain of loads, which 128x128 tiles stretch over more K tiles and fewer CUs; times at the dispatch.
+// update (EPI_EULER) among them.  Each of the eight waves takes one 16x16 fragment through the whole of K, so
+// that every output is summed in the order of the other tilings and the bits of a row do not depend on how many
+// rows the launch has.  K tiles of 128 reach LDS by loads that write it themselves, in a ring of up to five tiles
+// ahead: a K up to 640 is on its way as a whole before the first wait.  A lane ends with four consecutive columns
+// of one row, and what the epilogue reads of them (bias, pixels, residual) is read before the sums.  LN: the A rows
+// are adaLN of fp32 rows, normalised into LDS first (every column tile does it again, for less than a launch
+// costs).  Bound by the chain of loads, which 128x128 tiles stretch over more K tiles and fewer CUs; times at the
+// dispatch.
 namespace nar {
-constexpr int BM = 32, BN = 64, WAVES = 8, LDR = BN + 4;   // LDR: floats of a row of sums
+// The workgroup's barrier, for LDS accesses of the waves but not for their loads into LDS: behind the branches of a
+// wait for some of those loads, __syncthreads waits for all of them.
+__device__ __forceinline__ void ring_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+constexpr int BM = 32, BN = 64, WAVES = 8;
+template <int LN> constexpr int NST = LN ? 4 : 6;                              // stages of the ring, K = 128 each
+template <int LN> constexpr int HALF = (LN ? BN : BM + BN) * mf::BK * 2;       // bytes of K = 64: A rows (but LN), then W rows
+template <int LN> constexpr int ROWS = LN ? BM * (64 * LN + 8) * 2 : 0;        // bytes of LN's operand rows
+template <int LN> constexpr int LDS = ROWS<LN> + NST<LN> * 2 * HALF<LN>;
 }
 template <int EPI, int LN>   // LN: 0, or the 16-byte pieces a lane holds of an adaLN row (K <= 64 LN)
 __global__ __launch_bounds__(64 * nar::WAVES, 2) void k_linear_narrow(int M, int N, int K, const bf16 *__restrict__ A,
                                                                const bf16 *__restrict__ Wt, EpiArgs e, LnArgs ln) {
   using namespace nar;
-  __shared__ __attribute__((aligned(16))) float sums[WAVES][BM][LDR];
+  using mf::BK;
+  using mf::swz;
+  extern __shared__ __attribute__((aligned(16))) char smem_nar[];
+  bf16 *rows = reinterpret_cast<bf16 *>(smem_nar);   // LN: the operand rows, K + 8 apart (an odd number of 16-byte pieces)
+  char *ring = smem_nar + ROWS<LN>;
   const int tid = threadIdx.x, lane = tid & 63, fr = lane & 15, fq = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int m0 = blockIdx.x * BM, n0 = blockIdx.y * BN;
-  // rows past the end and columns past K read as zero
-  const __amdgpu_buffer_rsrc_t rsA = epi::rsrc(LN ? nullptr : A + (int64_t)m0 * K, LN ? 0u : (uint32_t)min(M - m0, BM) * (uint32_t)K * 2u);
-  const __amdgpu_buffer_rsrc_t rsW = epi::rsrc(Wt + (int64_t)n0 * K, (uint32_t)min(N - n0, BN) * (uint32_t)K * 2u);
-  const int chunks = (K + 63) / 64;
-  bf16 *rows = reinterpret_cast<bf16 *>(sums);   // LN: the operand rows, K + 8 apart (an odd number of 16-byte pieces)
-  u32x4 fa[2][2][2], fw[2][4][2];   // [buffer][16 rows][32 columns of K]
-  auto load = [&](int ch, int buf) {
+  // loads of a K tile, 8 rows of 128 bytes each: waves 0-3 one of A, waves 4-7 two of W; LN: every wave one of W.
+  // Rows past the end and columns past K read as zero.
+  const bool loads_a = LN == 0 && wave < 4;
+  const __amdgpu_buffer_rsrc_t rs = loads_a ? epi::rsrc(A + (int64_t)m0 * K, (uint32_t)min(M - m0, BM) * (uint32_t)K * 2u)
+                                            : epi::rsrc(Wt + (int64_t)n0 * K, (uint32_t)min(N - n0, BN) * (uint32_t)K * 2u);
+  const int row0 = loads_a ? 8 * wave : LN ? 8 * wave : 16 * (wave - 4);
+  char *dst0 = ring + ((LN || loads_a ? 0 : BM) + row0) * (BK * 2);
+  int kc[2];
+  uint32_t voff[2];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int k = 64 * ch + 32 * h + 8 * fq;
-      const uint32_t kb = k < K ? (uint32_t)k * 2u : epi::OUT_OF_RANGE;
-      if constexpr (LN == 0) {
+  for (int x = 0; x < 2; ++x) {
+    const int r = row0 + 8 * x + (lane >> 3);
+    kc[x] = ((lane & 7) ^ swz(r)) << 3;
+    voff[x] = (uint32_t)(r * K + kc[x]) * 2u;
+  }
+  auto load = [&](int kt, int st) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j) fa[buf][j][h] = __builtin_amdgcn_raw_buffer_load_b128(rsA, (uint32_t)((16 * j + fr) * K) * 2u + kb, 0, 0);
+    for (int y = 0; y < 2; ++y)
+#pragma unroll
+      for (int x = 0; x < (LN ? 1 : 2); ++x) {
+        if (x == 1 && loads_a) break;
+        const int k0 = (2 * kt + y) * BK;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(
+            rs, (__attribute__((address_space(3))) void *)(dst0 + (2 * st + y) * HALF<LN> + x * (8 * BK * 2)), 16,
+            k0 + kc[x] < K ? voff[x] : epi::OUT_OF_RANGE, k0 * 2, 0, 0);
       }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) fw[buf][i][h] = __builtin_amdgcn_raw_buffer_load_b128(rsW, (uint32_t)((16 * i + fr) * K) * 2u + kb, 0, 0);
-    }
   };
-  f32x4 acc[4][2];
+  const int KT = (K + 2 * BK - 1) / (2 * BK), mr = 16 * (wave & 1) + fr, nr = 16 * (wave >> 1) + fr;   // fragment rows of A and W
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0, 0, 0, 0};
-  auto mul = [&](int ch, int buf) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      if constexpr (LN != 0) {
-        const int k = 64 * ch + 32 * h;
-        if (k >= K) break;   // K % 32 == 0
-#pragma unroll
-        for (int j = 0; j < 2; ++j) fa[buf][j][h] = *reinterpret_cast<const u32x4 *>(rows + (16 * j + fr) * (K + 8) + k + 8 * fq);
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fw[buf][i][h]),
-                                                              __builtin_bit_cast(bf16x8, fa[buf][j][h]), acc[i][j], 0, 0, 0);
-    }
-  };
-  if (wave < chunks) load(wave, 0);
+  for (int t = 0; t < NST<LN> - 1; ++t)
+    if (t < KT) load(t, t);
   if constexpr (LN != 0) {
-    // the operand is adaLN of the fp32 rows (K <= 1024): a wave takes four rows, 16 lanes each, so that a
-    // row's two sums are four exchanges apiece and not six for every row in turn.  Lane l stands for lanes l, l + 16,
-    // l + 32 and l + 48 of k_ln_mod's row and adds in its order: the rows are the same to the bit.
-    static_assert(BM * (1024 + 8) * 2 <= sizeof(sums), "the rows fit the sums' LDS");
+    // the operand is adaLN of the fp32 rows: a wave takes four rows, 16 lanes each, so that a row's two sums are
+    // four exchanges apiece and not six for every row in turn.  Lane l stands for lanes l, l + 16, l + 32 and
+    // l + 48 of k_ln_mod's row and adds in its order: the rows are the same to the bit.
     const int nv = K >> 2, l16 = lane & 15, row = 4 * wave + (lane >> 4);
     const float4 *x = reinterpret_cast<const float4 *>(ln.x + (int64_t)min(m0 + row, M - 1) * K);
     float4 v[LN];
@@ -1332,54 +1343,59 @@ __global__ __launch_bounds__(64 * nar::WAVES, 2) void k_linear_narrow(int M, int
       }
       *reinterpret_cast<bf16x4 *>(rows + row * (K + 8) + 4 * c) = bf16x4{(bf16)o[0], (bf16)o[1], (bf16)o[2], (bf16)o[3]};
     }
-    __syncthreads();
   }
-  // EULER with p = 2: a wave takes every eighth pixel row of the tile's 32 tokens.  Other epilogues: a
-  // thread's 4 columns of one row.
-  const bool pairs = EPI == EPI_EULER && e.p == 2;
-  const int row = pairs ? lane >> 1 : tid >> 4, m = m0 + row, n = n0 + 4 * (tid & 15);
-  auto pixels = [&] {
-    if constexpr (EPI == EPI_EULER) return EulerPixels<BN / 2 / WAVES>(e, M, N, pairs ? m : M, n0, BN, wave, WAVES);
-    else return 0;
-  };
-  const auto px = pixels();
-  f32x4 h;
-  if constexpr (EPI == EPI_RESIDUAL) {
-    if (m < M && n < N) h = *reinterpret_cast<const f32x4 *>((e.res_in ? e.res_in : (const float *)e.out) + (int64_t)m * e.ldo + n);
-  }
-  for (int ch = wave; ch < chunks; ch += 2 * WAVES) {
-    if (ch + WAVES < chunks) load(ch + WAVES, 1);
-    mul(ch, 0);
-    if (ch + 2 * WAVES < chunks) load(ch + 2 * WAVES, 0);
-    if (ch + WAVES < chunks) mul(ch + WAVES, 1);
-  }
-  if constexpr (LN != 0) __syncthreads();   // every wave has read the rows
-  // acc[i][j]: columns 16 i + 4 fq .. + 3 of row 16 j + fr
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) *reinterpret_cast<f32x4 *>(&sums[wave][16 * j + fr][16 * i + 4 * fq]) = acc[i][j];
-  __syncthreads();
-  const int used = min(WAVES, chunks);
-  if constexpr (EPI == EPI_EULER) {
-    auto value = [&](int row, int col) {
-      float v = sums[0][row][col];
-      for (int w = 1; w < used; ++w) v += sums[w][row][col];
-      return e.bias ? v + e.bias[n0 + col] : v;
-    };
-    if (pairs) {
-      px.update(e, [&](int col) { return value(row, col); });
-    } else {
-      for (int x = tid; x < BM * BN; x += 64 * WAVES) {
-        const int r = x / BN, col = x % BN;
-        if (m0 + r < M && n0 + col < N) euler1(e, EulerRow(e, m0 + r).of_column(e, n0 + col), value(r, col));
+  // the lane's outputs: columns n .. n + 3 of row m
+  const int m = m0 + mr, n = n0 + 16 * (wave >> 1) + 4 * fq;
+  const bool live = m < M && n < N;
+  const bool pairs = EPI == EPI_EULER && e.p == 2;   // four columns are the 2 x 2 pixels of one channel
+  f32x4 bias = {0, 0, 0, 0}, h = bias;
+  int64_t z0 = 0, z1 = 0;
+  if (live) {
+    if (e.bias) bias = *reinterpret_cast<const f32x4 *>(e.bias + n);
+    if constexpr (EPI == EPI_RESIDUAL)
+      h = *reinterpret_cast<const f32x4 *>((e.res_in ? e.res_in : (const float *)e.out) + (int64_t)m * e.ldo + n);
+    if constexpr (EPI == EPI_EULER) {
+      if (pairs) {
+        const EulerRow r(e, m);
+        z0 = r.at(e, n >> 2, 0);
+        z1 = r.at(e, n >> 2, 1);
+        h = f32x4{e.z[z0], e.z[z0 + 1], e.z[z1], e.z[z1 + 1]};
       }
     }
+  }
+  f32x4 acc = {0, 0, 0, 0};
+  int st = 0;
+  for (int kt = 0; kt < KT; ++kt) {
+    // tile kt has landed once only the tiles after it may be in flight
+    const int ahead = min(NST<LN> - 2, KT - 1 - kt);
+    if (LN || loads_a) wait_tiles<2>(ahead);
+    else wait_tiles<4>(ahead);
+    ring_barrier();   // for every wave (LN: and the rows); nobody reads the stage of tile kt - 1 any more
+    if (kt + NST<LN> - 1 < KT) load(kt + NST<LN> - 1, st == 0 ? NST<LN> - 1 : st - 1);
+    bf16x8 fw[4], fa[4];   // columns past K are zero
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      const bf16 *half = reinterpret_cast<const bf16 *>(ring + (2 * st + (ks >> 1)) * HALF<LN>);
+      fw[ks] = *reinterpret_cast<const bf16x8 *>(half + (LN ? 0 : BM * BK) + mf::lds_off(nr, fq + 4 * (ks & 1)));
+      fa[ks] = LN ? *reinterpret_cast<const bf16x8 *>(rows + mr * (K + 8) + 2 * BK * kt + 32 * ks + 8 * fq)
+                  : *reinterpret_cast<const bf16x8 *>(half + mf::lds_off(mr, fq + 4 * (ks & 1)));
+    }
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      if (LN && 2 * BK * kt + 32 * ks >= K) break;   // K % 32 == 0
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[ks], fa[ks], acc, 0, 0, 0);
+    }
+    st = st + 1 == NST<LN> ? 0 : st + 1;
+  }
+  if (!live) return;
+  const f32x4 v = acc + bias;
+  EpiArgs r = e;
+  r.bias = nullptr;
+  if (pairs) {
+    euler2_from(e, z0, h[0], h[1], v[0], v[1]);
+    euler2_from(e, z1, h[2], h[3], v[2], v[3]);
   } else {
-    if (m >= M || n >= N) return;
-    f32x4 v = *reinterpret_cast<const f32x4 *>(&sums[0][row][n - n0]);
-    for (int w = 1; w < used; ++w) v += *reinterpret_cast<const f32x4 *>(&sums[w][row][n - n0]);
-    epilogue4<EPI, bf16>(e, m, n, v[0], v[1], v[2], v[3], EPI == EPI_RESIDUAL ? &h : nullptr);
+    epilogue4<EPI, bf16>(r, m, n, v[0], v[1], v[2], v[3], EPI == EPI_RESIDUAL ? &h : nullptr);
   }
 }
 
@@ -1987,11 +2003,24 @@ static hipError_t launch_f32(int M, int N, int K, const float *A, const float *W
   return hipGetLastError();
 }
 
+template <int EPI, int LN>
+static hipError_t launch_narrow_ln(int M, int N, int K, const void *A, const void *Wt, const EpiArgs &e, const LnArgs &ln,
+                                   hipStream_t s) {
+  auto kern = k_linear_narrow<EPI, LN>;
+  static bool attr_set = false;
+  if (!attr_set) {
+    hipError_t err = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, nar::LDS<LN>);
+    if (err != hipSuccess) return err;
+    attr_set = true;
+  }
+  const dim3 grid((M + nar::BM - 1) / nar::BM, (N + nar::BN - 1) / nar::BN);
+  hipLaunchKernelGGL(kern, grid, dim3(64 * nar::WAVES), nar::LDS<LN>, s, M, N, K, (const bf16 *)A, (const bf16 *)Wt, e, ln);
+  return hipGetLastError();
+}
+
 template <int EPI>
 static hipError_t launch_narrow(int M, int N, int K, const void *A, const void *Wt, const EpiArgs &e, hipStream_t s) {
-  const dim3 grid((M + nar::BM - 1) / nar::BM, (N + nar::BN - 1) / nar::BN);
-  hipLaunchKernelGGL((k_linear_narrow<EPI, 0>), grid, dim3(64 * nar::WAVES), 0, s, M, N, K, (const bf16 *)A, (const bf16 *)Wt, e, LnArgs{});
-  return hipGetLastError();
+  return launch_narrow_ln<EPI, 0>(M, N, K, A, Wt, e, LnArgs{}, s);
 }
 
 // bf16 operands, every epilogue but the latent scatter.
@@ -2074,27 +2103,24 @@ bool ln_linear_takes(ActType t, int M, int N, int D) {
 }
 
 template <int EPI>
-static void ln_linear(ActType t, int M, int N, int D, const LnArgs &ln, const void *Wt, const EpiArgs &e, hipStream_t s) {
+static hipError_t ln_linear(ActType t, int M, int N, int D, const LnArgs &ln, const void *Wt, const EpiArgs &e, hipStream_t s) {
   if (t == ACT_BF16) {
-    auto kern = D <= 256 ? k_linear_narrow<EPI, 4> : k_linear_narrow<EPI, 16>;
-    hipLaunchKernelGGL(kern, dim3((M + nar::BM - 1) / nar::BM, (N + nar::BN - 1) / nar::BN), dim3(64 * nar::WAVES), 0, s, M,
-                       N, D, nullptr, (const bf16 *)Wt, e, ln);
-  } else {
-    hipLaunchKernelGGL((k_linear_valu_dot<EPI, true>), dim3((M + 15) / 16, (N + 15) / 16), dim3(256), 0, s, M, N, D, nullptr,
-                       (const float *)Wt, e, ln);
+    return D <= 256 ? launch_narrow_ln<EPI, 4>(M, N, D, nullptr, Wt, e, ln, s) : launch_narrow_ln<EPI, 16>(M, N, D, nullptr, Wt, e, ln, s);
   }
+  hipLaunchKernelGGL((k_linear_valu_dot<EPI, true>), dim3((M + 15) / 16, (N + 15) / 16), dim3(256), 0, s, M, N, D, nullptr,
+                     (const float *)Wt, e, ln);
+  return hipGetLastError();
 }
 
 hipError_t launch_ln_linear(ActType t, int epi, int M, int N, int D, const LnArgs &ln, const void *Wt, const EpiArgs &e,
                             hipStream_t s) {
   switch (epi) {
-    case EPI_STORE: ln_linear<EPI_STORE>(t, M, N, D, ln, Wt, e, s); break;
-    case EPI_GELU: ln_linear<EPI_GELU>(t, M, N, D, ln, Wt, e, s); break;
-    case EPI_STORE_F32: ln_linear<EPI_STORE_F32>(t, M, N, D, ln, Wt, e, s); break;
-    case EPI_EULER: ln_linear<EPI_EULER>(t, M, N, D, ln, Wt, e, s); break;
+    case EPI_STORE: return ln_linear<EPI_STORE>(t, M, N, D, ln, Wt, e, s);
+    case EPI_GELU: return ln_linear<EPI_GELU>(t, M, N, D, ln, Wt, e, s);
+    case EPI_STORE_F32: return ln_linear<EPI_STORE_F32>(t, M, N, D, ln, Wt, e, s);
+    case EPI_EULER: return ln_linear<EPI_EULER>(t, M, N, D, ln, Wt, e, s);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 int describe_linear(ActType t, int epi, int M, int N, int K, char *buf, int len) {
@@ -2115,7 +2141,7 @@ int describe_linear(ActType t, int epi, int M, int N, int K, char *buf, int len)
     const TileChoice c = pick_tiles(M, N, K, dma_ok);
     const std::string nt = std::to_string((N + 255) / 256);
     if (c.plan == PLAN_NARROW) {
-      d = "k_linear_narrow: 32x64 tiles, K over 8 waves";
+      d = "k_linear_narrow: 32x64 tiles, one 16x16 fragment a wave";
     } else if (c.plan == PLAN_DEEP) {
       d = "k_linear_deep (8 waves): " + rows_of(c.wta) + "x" + std::to_string(64 * c.wt) + " tiles, " +
           std::to_string(c.nst) + " LDS stages";
