@@ -1407,8 +1407,10 @@ __global__ __launch_bounds__(64 * nar::WAVES, 2) void k_linear_narrow(int M, int
 // consecutive k of one row at once (k = 8 s + 4 g .. + 3, g = lane >> 5) and spends them on four MFMAs,
 // whose two k's are then 8 s + j and 8 s + 4 + j on both operands.  As in the bf16 kernels the weights
 // are the MFMA's row operand; their rows are taken in the order that leaves a lane eight consecutive
-// columns of one output row twice per 32-column fragment.  KS > 1: KS wave groups share a tile and take
-// every K tile's chunk pairs s in turn, their sums added through LDS in group order at the end.  Bound by
+// columns of one output row twice per 32-column fragment.  Each of a K tile's four chunk pairs s has a sum of
+// its own, the four being added in order at the end; KS = 4: four wave groups share a tile and hold one of the sums
+// each, added through LDS.  So every tiling rounds alike, and the bits of a row do not depend on how many rows the
+// launch has.  Bound by
 // the matrix cores (157 TFLOP/s nominal, a large library product reaches 154): 131 TFLOP/s at
 // (24960, 1536, 1536) on 64x64 tiles, five workgroups per CU.
 namespace mf32 {
@@ -1463,13 +1465,17 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void k_linear_f32(int M, in
   auto frag = [&](int st, int row, int s) {
     return *reinterpret_cast<const f32x4 *>(smem32 + st * STAGE + row * (BK * 4) + (((2 * s + g) ^ swz(row)) << 4));
   };
-  f32x16 acc[TN][TM];
+  static_assert(KS == 1 || KS == 4, "the chunk pairs of a K tile on one wave or on four");
+  constexpr int SUMS = 4 / KS;   // sums of a wave
+  f32x16 sum[SUMS][TN][TM];
 #pragma unroll
-  for (int i = 0; i < TN; ++i)
+  for (int s = 0; s < SUMS; ++s)
 #pragma unroll
-    for (int j = 0; j < TM; ++j)
+    for (int i = 0; i < TN; ++i)
 #pragma unroll
-      for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.f;
+      for (int j = 0; j < TM; ++j)
+#pragma unroll
+        for (int q = 0; q < 16; ++q) sum[s][i][j][q] = 0.f;
 
   const int KT = (K + BK - 1) / BK;
 #pragma unroll
@@ -1481,8 +1487,8 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void k_linear_f32(int M, in
     __syncthreads();                              // for every wave; nobody reads the stage of tile kt - 1 any more
     if (kt + NST - 1 < KT) load(kt + NST - 1, st == 0 ? NST - 1 : st - 1);
 #pragma unroll
-    for (int s = 0; s < 4 / KS; ++s) {
-      const int sp = s * KS + grp;
+    for (int s = 0; s < SUMS; ++s) {
+      const int sp = s + grp;
       f32x4 fa[TM], fw[TN];
 #pragma unroll
       for (int i = 0; i < TM; ++i) fa[i] = frag(st, 32 * TM * wm + 32 * i + li, sp);
@@ -1493,10 +1499,17 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void k_linear_f32(int M, in
 #pragma unroll
         for (int i = 0; i < TN; ++i)
 #pragma unroll
-          for (int j = 0; j < TM; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fw[i][q], fa[j][q], acc[i][j], 0, 0, 0);
+          for (int j = 0; j < TM; ++j) sum[s][i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fw[i][q], fa[j][q], sum[s][i][j], 0, 0, 0);
     }
     st = st + 1 == NST ? 0 : st + 1;
   }
+  f32x16 (&acc)[TN][TM] = sum[0];
+#pragma unroll
+  for (int s = 1; s < SUMS; ++s)
+#pragma unroll
+    for (int i = 0; i < TN; ++i)
+#pragma unroll
+      for (int j = 0; j < TM; ++j) acc[i][j] += sum[s][i][j];
   if constexpr (KS > 1) {
     static_assert(WGM * WGN == 1, "one tile per wave group");
     __syncthreads();   // every wave is past its last fragment reads: the ring is free
@@ -1526,120 +1539,147 @@ __global__ __launch_bounds__(64 * WGM * WGN * KS, 2) void k_linear_f32(int M, in
       [&](int cg, int rb, int q) { return acc[cg >> 1][rb][8 * (cg & 1) + q]; });
 }
 
-// 64x64 tiles, a thread computing 4 rows x 4 columns; K in steps of 16 staged in LDS with k outermost.
-// Takes operands at any 4-byte address and outputs of any width.
+// 64x64 tiles, a thread computing 4 rows x 4 columns; K in steps of 32 staged in LDS with k outermost, summed as
+// k_linear_f32 does: a sum for each of the four chunk pairs of a step, whose k's come in the order 0, 4, 1, 5, 2, 6,
+// 3, 7.  Takes operands at any 4-byte address and outputs of any width.
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
 template <int EPI>
 __global__ __launch_bounds__(256) void k_linear_valu(int M, int N, int K, const float *__restrict__ A,
                                                      const float *__restrict__ Wt, EpiArgs e) {
-  constexpr int T = 64, TK = 16;
+  constexpr int T = 64, TK = 32;
   __shared__ float sA[TK][T + 4];
   __shared__ float sW[TK][T + 4];
   const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
   const int m0 = blockIdx.x * T, n0 = blockIdx.y * T;
-  float acc[4][4] = {};
-  const int lr = tid >> 2, lk = (tid & 3) * 4;  // loader: row 0..63, 4 consecutive k
+  float acc[4][4][4] = {};   // [chunk pair][row][column]
+  const int lr = tid >> 2, lk = (tid & 3) * 8;  // loader: row 0..63, 8 consecutive k
   for (int k0 = 0; k0 < K; k0 += TK) {
-    const int k = k0 + lk;
-    f32x4u va = {0.f, 0.f, 0.f, 0.f}, vw = va;
-    if (m0 + lr < M && k < K) va = *reinterpret_cast<const f32x4u *>(A + (int64_t)(m0 + lr) * K + k);
-    if (n0 + lr < N && k < K) vw = *reinterpret_cast<const f32x4u *>(Wt + (int64_t)(n0 + lr) * K + k);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      sA[lk + q][lr] = va[q];
-      sW[lk + q][lr] = vw[q];
+    for (int h = 0; h < 2; ++h) {
+      const int k = k0 + lk + 4 * h;
+      f32x4u va = {0.f, 0.f, 0.f, 0.f}, vw = va;
+      if (m0 + lr < M && k < K) va = *reinterpret_cast<const f32x4u *>(A + (int64_t)(m0 + lr) * K + k);
+      if (n0 + lr < N && k < K) vw = *reinterpret_cast<const f32x4u *>(Wt + (int64_t)(n0 + lr) * K + k);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        sA[lk + 4 * h + q][lr] = va[q];
+        sW[lk + 4 * h + q][lr] = vw[q];
+      }
     }
     __syncthreads();
 #pragma unroll
-    for (int kk = 0; kk < TK; ++kk) {
-      float a[4], w[4];
+    for (int s = 0; s < 4; ++s)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = sA[kk][ty * 4 + i];
+      for (int x = 0; x < 8; ++x) {
+        const int k = 8 * s + (x >> 1) + 4 * (x & 1);
+        float a[4], w[4];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) w[j] = sW[kk][tx * 4 + j];
+        for (int i = 0; i < 4; ++i) a[i] = sA[k][ty * 4 + i];
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+        for (int j = 0; j < 4; ++j) w[j] = sW[k][tx * 4 + j];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], w[j], acc[i][j]);
-    }
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) acc[s][i][j] = fmaf(a[i], w[j], acc[s][i][j]);
+      }
     __syncthreads();
   }
   const int n = n0 + tx * 4;
   if (n >= N) return;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    int m = m0 + ty * 4 + i;
-    if (m < M) epilogue4<EPI, float>(e, m, n, acc[i][0], acc[i][1], acc[i][2], acc[i][3]);
+    const int m = m0 + ty * 4 + i;
+    float v[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = ((acc[0][i][j] + acc[1][i][j]) + acc[2][i][j]) + acc[3][i][j];
+    if (m < M) epilogue4<EPI, float>(e, m, n, v[0], v[1], v[2], v[3]);
   }
 }
 
 // 16x16 tiles, a thread computing a quarter of K of 1 row x 4 columns straight from memory: no LDS, no
-// barrier.  For the shortest sums, where a launch is little but its load latency.  LN: the operand is adaLN of
-// fp32 rows, made where it is used.
+// barrier.  For the shortest sums, where a launch is little but its load latency.  The quarter is one of the four
+// sums of k_linear_f32 (chunk pairs s, s + 4, ..), in its order.  LN: the operand is adaLN of fp32 rows, made where
+// it is used, its row sums added as k_ln_mod adds them.
 template <int EPI, bool LN>
 __global__ __launch_bounds__(256) void k_linear_valu_dot(int M, int N, int K, const float *__restrict__ A,
                                                          const float *__restrict__ Wt, EpiArgs e, LnArgs ln) {
   const int tid = threadIdx.x, part = tid & 3;
   const int m = blockIdx.x * 16 + (tid >> 4), n = blockIdx.y * 16 + 4 * ((tid >> 2) & 3);
   const bool live = m < M && n < N;   // N % 4 == 0
-  const int c4 = K / 4;
+  const int c4 = K / 4, pairs = K / 8;   // K % 8 == 0
   const f32x4u *w = reinterpret_cast<const f32x4u *>(Wt + (int64_t)(live ? n : 0) * K);
   float acc[4] = {};
-  auto chunk = [&](int c, f32x4u x) {
+  auto pair = [&](int s, f32x4u x0, f32x4u x1) {   // pieces 2 s and 2 s + 1
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const f32x4u y = w[j * c4 + c];
+      const f32x4u y0 = w[j * c4 + 2 * s], y1 = w[j * c4 + 2 * s + 1];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) acc[j] = fmaf(x[q], y[q], acc[j]);
+      for (int q = 0; q < 4; ++q) acc[j] = fmaf(x1[q], y1[q], fmaf(x0[q], y0[q], acc[j]));
     }
   };
   if constexpr (LN != 0) {
-    // the operand is adaLN of the fp32 row (K <= 64), whose quarters the four lanes of an output hold: piece c of
-    // the row belongs to lane c of k_ln_mod, which adds c ^ 8, c ^ 4, c ^ 2 and c ^ 1 in turn
+    // the operand is adaLN of the fp32 row (K <= 64), whose chunk pairs part and part + 4 this lane holds: piece c
+    // of the row belongs to lane c of k_ln_mod, which adds c ^ 8, c ^ 4, c ^ 2 and c ^ 1 in turn
     const f32x4u *a = reinterpret_cast<const f32x4u *>(ln.x + (int64_t)min(m, M - 1) * K);
-    f32x4u x[4];
-    float s[4], q2[4] = {};
-    auto row_sum = [](const float (&t)[4]) {
-      float u = (t[0] + t[2]) + (t[1] + t[3]);
-      u += __shfl_xor(u, 2, 64);
-      return u + __shfl_xor(u, 1, 64);
-    };
+    f32x4u x[2][2];   // [pair][piece]
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      x[i] = part + 4 * i < c4 ? a[part + 4 * i] : f32x4u{0.f, 0.f, 0.f, 0.f};
-      s[i] = (x[i][0] + x[i][1]) + (x[i][2] + x[i][3]);
+      const int c = 2 * (part + 4 * (i >> 1)) + (i & 1);
+      x[i >> 1][i & 1] = c < c4 ? a[c] : f32x4u{0.f, 0.f, 0.f, 0.f};
     }
-    const float mean = row_sum(s) / (float)K;
+    auto row_sum = [](const float (&t)[2][2]) {
+      float u[2];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      if (part + 4 * i < c4) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) x[i][q] -= mean;
-        q2[i] = sum_sq4(x[i][0], x[i][1], x[i][2], x[i][3]);
+      for (int b = 0; b < 2; ++b) {
+        u[b] = t[0][b] + t[1][b];
+        u[b] += __shfl_xor(u[b], 2, 64);
+        u[b] += __shfl_xor(u[b], 1, 64);
       }
-    const float rstd = 1.0f / sqrtf(row_sum(q2) / (float)K + ln.eps);
+      return u[0] + u[1];
+    };
+    float t[2][2];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int c = part + 4 * i;
-      if (!live || c >= c4) break;
-      f32x4u y = x[i] * rstd;
-      if (ln.shift) {
-        const f32x4u sc = reinterpret_cast<const f32x4u *>(ln.scale)[c], sh = reinterpret_cast<const f32x4u *>(ln.shift)[c];
+      const f32x4u &y = x[i >> 1][i & 1];
+      t[i >> 1][i & 1] = (y[0] + y[1]) + (y[2] + y[3]);
+    }
+    const float mean = row_sum(t) / (float)K;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) y[q] = fmaf(y[q], 1.0f + sc[q], sh[q]);
+    for (int i = 0; i < 4; ++i) {
+      f32x4u &y = x[i >> 1][i & 1];
+      const int c = 2 * (part + 4 * (i >> 1)) + (i & 1);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) y[q] -= mean;
+      t[i >> 1][i & 1] = c < c4 ? sum_sq4(y[0], y[1], y[2], y[3]) : 0.f;
+    }
+    const float rstd = 1.0f / sqrtf(row_sum(t) / (float)K + ln.eps);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int s = part + 4 * h;
+      if (!live || s >= pairs) break;
+      f32x4u y[2];
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        y[b] = x[h][b] * rstd;
+        if (ln.shift) {
+          const f32x4u sc = reinterpret_cast<const f32x4u *>(ln.scale)[2 * s + b], sh = reinterpret_cast<const f32x4u *>(ln.shift)[2 * s + b];
+#pragma unroll
+          for (int q = 0; q < 4; ++q) y[b][q] = fmaf(y[b][q], 1.0f + sc[q], sh[q]);
+        }
       }
-      chunk(c, y);
+      pair(s, y[0], y[1]);
     }
   } else if (live) {
     const f32x4u *a = reinterpret_cast<const f32x4u *>(A + (int64_t)m * K);
-#pragma unroll 4
-    for (int c = part; c < c4; c += 4) chunk(c, a[c]);
+#pragma unroll 2
+    for (int s = part; s < pairs; s += 4) pair(s, a[2 * s], a[2 * s + 1]);
   }
+  // the four sums in order, for the lane of the first
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    acc[j] += __shfl_xor(acc[j], 1, 64);
-    acc[j] += __shfl_xor(acc[j], 2, 64);
+    const float a1 = __shfl_down(acc[j], 1, 64), a2 = __shfl_down(acc[j], 2, 64), a3 = __shfl_down(acc[j], 3, 64);
+    acc[j] = ((acc[j] + a1) + a2) + a3;
   }
   if (live && part == 0) epilogue4<EPI, float>(e, m, n, acc[0], acc[1], acc[2], acc[3]);
 }

@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 CODE = {"bf16": F.BF16, "fp32": F.FP32}
 ACT = {"bf16": torch.bfloat16, "fp32": torch.float32}
-TILES = {"bf16": ["narrow", "128x128", "256x256"]}
+TILES = {"bf16": ["narrow", "128x128", "256x256"], "fp32": ["f32:64x64", "f32:32x32", "f32:dot", "f32:valu"]}
 
 
 def _operands(dtype, M, N, K):
@@ -63,7 +63,7 @@ def test_rows(dtype, N, K, epi, monkeypatch):
     for M in (3, 40, 500, 9000):
         plans.add(F.flashbon_op_linear_plan(CODE[dtype], M, N, K, F.EPI_STORE)[1])
         outs.append(_layer(dtype, a[:M], w, bias, gate, h[:M], epi)[:3])
-    assert len(plans) > 1
+    assert len(plans) > 1 or (dtype == "fp32" and N < 1536)
     for o in outs[1:]:
         assert torch.equal(o, outs[0])
 
