@@ -17,6 +17,7 @@
 //     consecutive head dims of one key and lane 4a + b receives element b of the pieces addressed by
 //     lanes a, a + 4, a + 8, a + 12 -- i.e. one head dim across four keys.  Keys are taken in tiles of
 //     64 with an online softmax; the order of a wave's work is described at the kernel.
+#include <algorithm>
 #include <cstdlib>
 #include <cstring>
 #include <type_traits>
@@ -730,22 +731,28 @@ static hipError_t launch_f32_slabs(AttnP p, hipStream_t s) {
 // LDS, which pays them in every round.  Measured (1, 2, 4 slabs): head dim 128, 12 heads of 400 x 400 64, 40,
 // 29 us; 2 x 12 heads of 1560 x 1560 415, 335, 376; 4 x 12 heads of 1560 x 512 221, 189, 277; 32 heads of
 // 1000 x 77 25, 28, 49; 2 heads of 4096 x 4096 571, 305, 182; head dim 16, 32 heads of 700 x 700 32, 29, 24.
+// The split sets the order of a query's sums, so it goes by the shape of one batch row, at the least mean square of
+// the cost over the best split's for pools of 1 to 16, and a candidate's bits do not depend on the pool it is in.
 static int attn_slabs(const AttnP &p, int dh) {
   // FLASHBON_ATTN_F32 (tests and tuning): "valu" or the number of slabs
   const char *force = getenv("FLASHBON_ATTN_F32");
   if (force && (atoi(force) == 1 || atoi(force) == 2 || atoi(force) == 4)) return atoi(force);
-  int cus = 256, dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
-    cus = 256;
+  const int cus = cu_count();
   const double mfma = (dh / 2 + 16.0 * (dh < 32 ? 1 : dh / 32)) / 128 + (dh < 128 ? 0.06 : 0.0);
-  auto cost = [&](int slabs, double tile, double fixed) {
-    const int64_t wgs = (int64_t)p.batch * p.heads * ((p.tq + 128 / slabs - 1) / (128 / slabs));
+  auto cost = [&](int batch, int slabs, double tile, double fixed) {
+    const int64_t wgs = (int64_t)batch * p.heads * ((p.tq + 128 / slabs - 1) / (128 / slabs));
     const double rounds = (double)((wgs + cus - 1) / cus), tiles = (p.tk + 32 * slabs - 1) / (32 * slabs);
     return rounds * tiles * tile * mfma + fixed * (slabs == 4 && dh == 128 ? rounds : 1);
   };
-  const double c1 = cost(1, 4.7, 5.0), c2 = cost(2, 4.7, 6.5), c4 = cost(4, 5.4, dh == 128 ? 9.0 : 5.0);
-  return c1 <= c2 && c1 <= c4 ? 1 : c2 <= c4 ? 2 : 4;
+  double over1 = 0, over2 = 0, over4 = 0;   // (cost / least cost)^2, summed over the pool sizes
+  for (int batch = 1; batch <= 16; batch *= 2) {
+    const double c1 = cost(batch, 1, 4.7, 5.0), c2 = cost(batch, 2, 4.7, 6.5), c4 = cost(batch, 4, 5.4, dh == 128 ? 9.0 : 5.0);
+    const double best = std::min(c1, std::min(c2, c4));
+    over1 += c1 * c1 / (best * best);
+    over2 += c2 * c2 / (best * best);
+    over4 += c4 * c4 / (best * best);
+  }
+  return over1 <= over2 && over1 <= over4 ? 1 : over2 <= over4 ? 2 : 4;
 }
 
 template <typename T, int DH>

@@ -1704,7 +1704,6 @@ struct TileChoice {
   int waves = 4;   // PLAN_MIX: the 4-wave (k_linear_dma) or the 8-wave (k_linear_dma8) kernel
   int wt = 4, nst = 2;   // PLAN_DEEP: (32 wta) x (64 wt) tiles, nst LDS stages
 };
-static int cu_count();
 // Whether a layer is at most one 32x64 tile per CU and its K whole MFMA steps.
 static bool narrow_fits(int M, int N, int K) {
   return K % 32 == 0 && (int64_t)((M + 31) / 32) * ((N + 63) / 64) <= cu_count();
@@ -1962,7 +1961,7 @@ static hipError_t launch_deep(int M, int N, int K, const void *A, const void *Wt
   return hipGetLastError();
 }
 
-static int cu_count() {
+int cu_count() {
   static int n = 0;
   if (!n) {
     int dev = 0, v = 0;

@@ -54,6 +54,9 @@ struct LnArgs {
 bool ln_linear_takes(ActType t, int M, int N, int D);
 hipError_t launch_ln_linear(ActType t, int epi, int M, int N, int D, const LnArgs &ln, const void *Wt, const EpiArgs &e,
                             hipStream_t s);
+// Compute units of the current device (asked once).
+int cu_count();
+
 // The kernels launch_linear would use for this shape, without launching: returns the number of
 // launches and writes a NUL-terminated description (truncated to len - 1 characters) into buf.
 int describe_linear(ActType t, int epi, int M, int N, int K, char *buf, int len);

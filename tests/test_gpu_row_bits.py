@@ -68,8 +68,10 @@ def test_rows(dtype, N, K, epi, monkeypatch):
         assert torch.equal(o, outs[0])
 
 
-# one candidate alone and in pools of 2 and 7: the head (and with small widths every layer) changes its kernel
-@pytest.mark.parametrize("dtype,hidden,heads", [("bf16", 128, 1)])
+# one candidate alone and in pools of 2 and 7: the head (and with small widths every layer) changes its kernel, and
+# 2 heads of 1369 tokens would each be split differently between the waves of a workgroup
+@pytest.mark.parametrize("dtype,hidden,heads", [("bf16", 128, 1), ("bf16", 128, 2), ("bf16", 64, 4), ("fp32", 256, 2),
+                                                ("fp32", 64, 4)])
 @pytest.mark.parametrize("rope", [False, True])
 def test_pools(dtype, hidden, heads, rope):
     shape = synth.ModelShape(num_blocks=2, hidden=hidden, heads=heads, mlp_hidden=192, freq_dim=32, text_dim=32,
