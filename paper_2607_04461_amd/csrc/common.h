@@ -36,8 +36,9 @@ __device__ __forceinline__ float gelu_tanh(float x) {
 
 __device__ __forceinline__ float silu(float x) { return x / (1.0f + __expf(-x)); }
 
-// Sum of four squares.  Which products are fused is written out: left to the compiler it differs from kernel to
-// kernel, and rows that two kernels form would differ in their last bits.
+// Sums of four products and of four squares.  Which products are fused is written out: left to the compiler it
+// differs from kernel to kernel, and rows that two kernels form would differ in their last bits.
+__device__ __forceinline__ float dot4(float4 a, float4 b) { return fmaf(a.y, b.y, a.x * b.x) + fmaf(a.z, b.z, a.w * b.w); }
 __device__ __forceinline__ float sum_sq4(float a, float b, float c, float d) { return fmaf(a, a, b * b) + fmaf(c, c, d * d); }
 
 // wave64 reductions

@@ -302,10 +302,10 @@ __global__ __launch_bounds__(256) void k_qk_norm(int M, int D, int dh, T *__rest
       for (int h = 0; h < 2; ++h) {
         const float4 t = cs[h];   // (cos, sin) of two pairs
         const float a = v[i][4 * h], b = v[i][4 * h + 1], d = v[i][4 * h + 2], e = v[i][4 * h + 3];
-        v[i][4 * h] = a * t.x - b * t.y;
-        v[i][4 * h + 1] = a * t.y + b * t.x;
-        v[i][4 * h + 2] = d * t.z - e * t.w;
-        v[i][4 * h + 3] = d * t.w + e * t.z;
+        v[i][4 * h] = fmaf(a, t.x, -(b * t.y));
+        v[i][4 * h + 1] = fmaf(b, t.x, a * t.y);
+        v[i][4 * h + 2] = fmaf(d, t.z, -(e * t.w));
+        v[i][4 * h + 3] = fmaf(e, t.z, d * t.w);
       }
     }
     store8<T>(xr + 8 * c, v[i]);
@@ -338,26 +338,33 @@ hipError_t launch_qk_norm(ActType t, int M, int D, int dh, void *x0, void *x1, i
 // six launches -- features, each product and the block tables on their own -- it took 44 and 16.
 
 // e1 = SiLU(W f + b) with the sinusoidal features f[j] = cos(a), f[half + j] = sin(a), a = 1000 t 10000^(-j/half)
-// (computed in double by every workgroup, kFeat at a time); one wave per output row.
-constexpr int kFeat = 512;
+// (computed in double by every workgroup, kFeat at a time); one wave per output row, which it sums as wave_dots does.
+constexpr int kFeat = 1024;   // the float4s of four chunks of a wave
 __global__ __launch_bounds__(256) void k_time_mlp1(double t, int half, int out, const float *__restrict__ W,
                                                    const float *__restrict__ b, float *__restrict__ y) {
-  __shared__ float fc[kFeat], fs[kFeat];
+  __shared__ __attribute__((aligned(16))) float f[kFeat];
   const int lane = threadIdx.x & 63, o = blockIdx.x * 4 + (threadIdx.x >> 6);
   const float *wr = W + (int64_t)min(o, out - 1) * 2 * half;
-  float acc = 0.f;
-  for (int j0 = 0; j0 < half; j0 += kFeat) {
-    const int n = min(kFeat, half - j0);
+  float part[4] = {};
+  for (int j0 = 0; j0 < 2 * half; j0 += kFeat) {
+    const int n = min(kFeat, 2 * half - j0);
     if (j0) __syncthreads();
-    for (int j = threadIdx.x; j < n; j += 256) {
-      const double w = pow(10000.0, -(double)(j0 + j) / (double)half), a = 1000.0 * t * w;
-      fc[j] = (float)cos(a);
-      fs[j] = (float)sin(a);
+    for (int i = threadIdx.x; i < n; i += 256) {
+      const int j = j0 + i < half ? j0 + i : j0 + i - half;
+      const double w = pow(10000.0, -(double)j / (double)half), a = 1000.0 * t * w;
+      f[i] = (float)(j0 + i < half ? cos(a) : sin(a));
     }
     __syncthreads();
-    for (int j = lane; j < n; j += 64) acc += wr[j0 + j] * fc[j] + wr[half + j0 + j] * fs[j];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int k = lane + 64 * u;
+      if (4 * k < n) {   // freq_dim % 8 == 0
+        const float4 w = reinterpret_cast<const float4 *>(wr + j0)[k], xv = reinterpret_cast<const float4 *>(f)[k];
+        part[u] += dot4(w, xv);
+      }
+    }
   }
-  acc = wave_sum(acc);
+  const float acc = wave_sum((part[0] + part[1]) + (part[2] + part[3]));
   if (lane == 0 && o < out) y[o] = silu(acc + b[o]);
 }
 
@@ -366,12 +373,13 @@ hipError_t launch_time_mlp1(double t, int freq_dim, int out, const float *W, con
   return hipGetLastError();
 }
 
-// acc[r] = row r . x for R consecutive rows of one wave (every lane ends with all R): 16-byte loads, U chunks
-// of each row in flight per lane, so that a wave streams its rows at the memory rate; SILU: x goes through
-// SiLU first.  in % 4 == 0, 16-byte aligned.
-template <bool SILU, int R, int U>
+// acc[r] = row r . x for R consecutive rows of one wave (every lane ends with all R): 16-byte loads, four chunks
+// of each row in flight per lane and a partial sum for each of them, so that a wave streams its rows at the memory
+// rate; SILU: x goes through SiLU first.  in % 4 == 0, 16-byte aligned.
+template <bool SILU, int R>
 __device__ __forceinline__ void wave_dots(const float *__restrict__ rows, const float *__restrict__ x, int in, int lane,
                                           float (&acc)[R]) {
+  constexpr int U = 4;
   const float4 *xr = reinterpret_cast<const float4 *>(x), *wr = reinterpret_cast<const float4 *>(rows);
   const int n4 = in >> 2;
   float part[R][U] = {};
@@ -391,17 +399,11 @@ __device__ __forceinline__ void wave_dots(const float *__restrict__ rows, const 
       if (k0 + 64 * u >= n4) break;
       if constexpr (SILU) xv[u] = make_float4(silu(xv[u].x), silu(xv[u].y), silu(xv[u].z), silu(xv[u].w));
 #pragma unroll
-      for (int r = 0; r < R; ++r)
-        part[r][u] += (w[r][u].x * xv[u].x + w[r][u].y * xv[u].y) + (w[r][u].z * xv[u].z + w[r][u].w * xv[u].w);
+      for (int r = 0; r < R; ++r) part[r][u] += dot4(w[r][u], xv[u]);
     }
   }
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    acc[r] = part[r][0];
-#pragma unroll
-    for (int u = 1; u < U; ++u) acc[r] += part[r][u];
-    acc[r] = wave_sum(acc[r]);
-  }
+  for (int r = 0; r < R; ++r) acc[r] = wave_sum((part[r][0] + part[r][1]) + (part[r][2] + part[r][3]));
 }
 
 __global__ __launch_bounds__(256) void k_time_mlp2(int D, const float *__restrict__ W, const float *__restrict__ b,
@@ -409,7 +411,7 @@ __global__ __launch_bounds__(256) void k_time_mlp2(int D, const float *__restric
   const int lane = threadIdx.x & 63, o = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (o >= D) return;
   float a[1];
-  wave_dots<false, 1, 4>(W + (int64_t)o * D, x, D, lane, a);
+  wave_dots<false, 1>(W + (int64_t)o * D, x, D, lane, a);
   if (lane == 0) y[o] = a[0] + b[o];
 }
 
@@ -432,7 +434,7 @@ __global__ __launch_bounds__(256) void k_modulations(int L, int D, const float *
   const float *W = head ? Wh : Wm, *b = head ? bh : bm;
   const int row0 = head ? o0 - width : o0;
   float a[4];
-  wave_dots<true, 4, 3>(W + (int64_t)(row0 + 4 * wave) * D, e, D, lane, a);
+  wave_dots<true, 4>(W + (int64_t)(row0 + 4 * wave) * D, e, D, lane, a);
 #pragma unroll
   for (int r = 0; r < 4; ++r)
     if (lane == r) m[4 * wave + r] = a[r] + b[row0 + 4 * wave + r];
