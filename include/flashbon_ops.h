@@ -44,10 +44,10 @@ flashbon_status flashbon_op_linear_residual(int32_t dtype, int32_t M, int32_t N,
 
 /* flashbon_op_linear with a caller-owned workspace (device, workspace_bytes) for split-K partial sums,
  * as the draft and refinement steps run their linear layers: a bf16 shape whose 224 x 256 tiles would
- * fill less than half the CUs (one candidate's MLP down-projection, M = 1560, N = 1536, K = 8960), and that
- * gains at least a quarter more workgroups by it, is cut into K ranges of at least 16 x 64 columns, each
- * range's fp32 partial sums stored in the workspace (splits x M x N x 4 bytes, at most 48 MiB), then added
- * in range order before the epilogue; other
+ * fill less than half the CUs (one candidate's MLP down-projection, M = 1560, N = 1536, K = 8960) is cut
+ * into K ranges of at least 16 x 64 columns, each range's fp32 partial sums stored in the workspace
+ * (splits x M x N x 4 bytes, at most 48 MiB), then added in range order before the epilogue (ranges that bring
+ * less than a quarter more workgroups are added in the same order without the workspace); other
  * shapes, and a workspace too small for the plan, run exactly as flashbon_op_linear.  *splits (optional)
  * receives the number of K ranges used (1 = none).  Arguments otherwise as flashbon_op_linear; the
  * workspace must not overlap any other buffer. */

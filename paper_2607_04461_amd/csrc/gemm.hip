@@ -64,6 +64,13 @@ __device__ __forceinline__ void euler2(const EpiArgs &e, int64_t zi, float v0, f
   euler2_from(e, zi, z0[0], z0[1], v0, v1);
 }
 
+// h + g v with the product rounded on its own: the residual update of a layer whose K ranges are added up, on the
+// split-K reduction and on the tile that takes the ranges in turn
+__device__ __forceinline__ float add_product(float h, float g, float v) {
+#pragma clang fp contract(off)
+  return h + g * v;
+}
+
 template <int EPI, typename TO>
 __device__ __forceinline__ void epilogue4(const EpiArgs &e, int m, int n, float v0, float v1,
                                           float v2, float v3, const f32x4 *residual = nullptr) {
@@ -164,8 +171,10 @@ __device__ __forceinline__ void epilogue8(const EpiArgs &e, int m, int n, const 
       if (e.gate) {
         float4 g0 = *reinterpret_cast<const float4 *>(e.gate + n);
         float4 g1 = *reinterpret_cast<const float4 *>(e.gate + n + 4);
-        h0.x += g0.x * v[0]; h0.y += g0.y * v[1]; h0.z += g0.z * v[2]; h0.w += g0.w * v[3];
-        h1.x += g1.x * v[4]; h1.y += g1.y * v[5]; h1.z += g1.z * v[6]; h1.w += g1.w * v[7];
+        h0 = make_float4(add_product(h0.x, g0.x, v[0]), add_product(h0.y, g0.y, v[1]), add_product(h0.z, g0.z, v[2]),
+                         add_product(h0.w, g0.w, v[3]));
+        h1 = make_float4(add_product(h1.x, g1.x, v[4]), add_product(h1.y, g1.y, v[5]), add_product(h1.z, g1.z, v[6]),
+                         add_product(h1.w, g1.w, v[7]));
       } else {
         h0.x += v[0]; h0.y += v[1]; h0.z += v[2]; h0.w += v[3];
         h1.x += v[4]; h1.y += v[5]; h1.z += v[6]; h1.w += v[7];
@@ -317,7 +326,8 @@ __device__ __forceinline__ void residual_tile(const EpiArgs &e, int M, int N, in
 // element).  lds: the K-loop's ring, free once every wave is past its last fragment reads (the barrier);
 // a wave reuses its region for the next column group without one, its LDS accesses completing in order.
 // Batches of B read-back rows, the residual loads of batch b + 1 issued before the stores of batch b.
-template <int NCG, int WTA, int CM, int POL>
+// RANGES: rounded as the split-K reduction rounds.
+template <int NCG, int WTA, int CM, int POL, bool RANGES = false>
 __device__ __forceinline__ void residual_staged(const EpiArgs &e, const f32x4 (&acc)[2 * NCG][WTA], int M, int N,
                                                 int mbase, int nbase, int fr, int fq, int lane, int wave,
                                                 char *lds) {
@@ -371,7 +381,7 @@ __device__ __forceinline__ void residual_staged(const EpiArgs &e, const f32x4 (&
         const f32x4 a = *reinterpret_cast<const f32x4 *>(wl + r * 128 + ((k ^ (r & 7)) << 4));
         f32x4 o = h[buf][i];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) o[q] += gg[q] * (a[q] + bb[q]);
+        for (int q = 0; q < 4; ++q) o[q] = RANGES ? add_product(o[q], gg[q], a[q] + bb[q]) : fmaf(gg[q], a[q] + bb[q], o[q]);
         const uint32_t off = r0 + (uint32_t)t * rstep + cn;
         st4<POL>(rsO, off, o);
         if constexpr (CM == 1) st4<POL>(rsC, off, o);
@@ -965,10 +975,11 @@ __device__ __forceinline__ void wait_tiles(int n) {
 }
 
 // One (32 WTA) x (64 WT) tile on 8 waves in a 2 (m) x 4 (n) grid of (16 WTA) x (16 WT) wave tiles, K tiles
-// of 64 through an LDS ring of NST stages, each K tile's loads issued NST - 1 tiles ahead.
-template <int EPI, typename TO, int WTA, int WT = 4, int NST = 2, int POL = 0>
+// of 64 through an LDS ring of NST stages, each K tile's loads issued NST - 1 tiles ahead.  RANGES: every
+// `range` K tiles have a sum of their own, the sums added in order (as the split-K launch adds its ranges).
+template <int EPI, typename TO, int WTA, int WT = 4, int NST = 2, int POL = 0, bool RANGES = false>
 __device__ __forceinline__ void dma8_tile(int M, int N, int K, const bf16 *__restrict__ A, const bf16 *__restrict__ Wt,
-                                          const EpiArgs &e, int m0, int n0, bf16 *smem, int ldk) {
+                                          const EpiArgs &e, int m0, int n0, bf16 *smem, int ldk, int range = 0) {
   // K: columns accumulated (K % 64 == 0, K >= 128); ldk: row stride of A and Wt in elements (ldk >= K;
   // larger for one K range of a split-K launch, whose A and Wt point at the range's first column)
   using namespace mf;
@@ -1070,6 +1081,31 @@ __device__ __forceinline__ void dma8_tile(int M, int N, int K, const bf16 *__res
 #pragma unroll
     for (int j = 0; j < WTA; ++j) acc[i][j] = f32x4{0, 0, 0, 0};
   int kt = 0, last;   // last: the stage of the last K tile
+  f32x4 total[RANGES ? WT : 1][RANGES ? WTA : 1];
+  int bound = range;
+  auto add_range = [&] {
+#pragma unroll
+    for (int i = 0; i < (RANGES ? WT : 0); ++i)
+#pragma unroll
+      for (int j = 0; j < (RANGES ? WTA : 0); ++j) {
+        total[i][j] += acc[i][j];
+        acc[i][j] = f32x4{0, 0, 0, 0};
+      }
+  };
+  auto at_tile = [&](int t) {   // before the first product of K tile t
+    if constexpr (RANGES) {
+      if (t != bound) return;
+      add_range();
+      bound += range;
+    }
+  };
+  if constexpr (RANGES) {
+    static_assert(NST == 3, "the three-stage loop marks its K tiles");
+#pragma unroll
+    for (int i = 0; i < WT; ++i)
+#pragma unroll
+      for (int j = 0; j < WTA; ++j) total[i][j] = f32x4{0, 0, 0, 0};
+  }
   if constexpr (NST == 2) {
     for (; kt + 2 < KT; ++kt) {
       substep(T_{}, F_{}, fw0, fa0, kt & 1, 1, fw1, fa1, 0, 0);
@@ -1087,6 +1123,7 @@ __device__ __forceinline__ void dma8_tile(int M, int N, int K, const bf16 *__res
     // wave has finished reading by the barrier.
     int st = 0;
     for (; kt + NST < KT; ++kt) {
+      at_tile(kt);
       const int nx = st + 1 == NST ? 0 : st + 1;
       substep(T_{}, F_{}, fw0, fa0, st, 1, fw1, fa1, 0, 0);
       if (loads_a) wait_tiles<WTA>(NST - 2);   // tile kt+1 has landed
@@ -1096,6 +1133,7 @@ __device__ __forceinline__ void dma8_tile(int M, int N, int K, const bf16 *__res
       st = nx;
     }
     for (; kt + 1 < KT; ++kt) {   // no loads left to issue; tiles kt+2 .. KT-1 may still be in flight
+      at_tile(kt);
       const int nx = st + 1 == NST ? 0 : st + 1;
       substep(T_{}, F_{}, fw0, fa0, st, 1, fw1, fa1, 0, 0);
       if (loads_a) wait_tiles<WTA>(KT - 2 - kt);
@@ -1106,8 +1144,15 @@ __device__ __forceinline__ void dma8_tile(int M, int N, int K, const bf16 *__res
     }
     last = st;
   }
+  at_tile(KT - 1);
   substep(T_{}, F_{}, fw0, fa0, last, 1, fw1, fa1, 0, 0);
   substep(F_{}, F_{}, fw1, fa1, 0, 0, fw0, fa0, 0, 0);
+  if constexpr (RANGES) {
+#pragma unroll
+    for (int i = 0; i < WT; ++i)
+#pragma unroll
+      for (int j = 0; j < WTA; ++j) acc[i][j] = total[i][j] + acc[i][j];
+  }
   if constexpr (EPI == EPI_EULER) {
     static_assert(BM * (BN + 4) * 4 <= NST * STAGE * 2, "the tile fits the ring");
     euler_staged<WTA, WT>(e, acc, M, N, m0, n0, wm, wn, fr, fq, lane, wave, reinterpret_cast<char *>(smem));
@@ -1116,9 +1161,9 @@ __device__ __forceinline__ void dma8_tile(int M, int N, int K, const bf16 *__res
     // (all tiles but 160 x 128 with 2 stages)
     char *lw = reinterpret_cast<char *>(smem);
     const int mb = m0 + 16 * WTA * wm, nb = n0 + 16 * WT * wn;
-    if (!e.cache) residual_staged<WT / 2, WTA, 0, POL>(e, acc, M, N, mb, nb, fr, fq, lane, wave, lw);
-    else if (!e.cache_delta) residual_staged<WT / 2, WTA, 1, POL>(e, acc, M, N, mb, nb, fr, fq, lane, wave, lw);
-    else residual_staged<WT / 2, WTA, 2, POL>(e, acc, M, N, mb, nb, fr, fq, lane, wave, lw);
+    if (!e.cache) residual_staged<WT / 2, WTA, 0, POL, RANGES>(e, acc, M, N, mb, nb, fr, fq, lane, wave, lw);
+    else if (!e.cache_delta) residual_staged<WT / 2, WTA, 1, POL, RANGES>(e, acc, M, N, mb, nb, fr, fq, lane, wave, lw);
+    else residual_staged<WT / 2, WTA, 2, POL, RANGES>(e, acc, M, N, mb, nb, fr, fq, lane, wave, lw);
   } else if constexpr ((EPI == EPI_STORE || EPI == EPI_GELU) && sizeof(TO) == 2 && WT == 4 &&
                        8 * 16 * WTA * 128 <= NST * STAGE * 2) {
     store_staged<EPI, WTA, POL>(e, acc, M, N, m0 + 16 * WTA * wm, n0 + 16 * WT * wn, fr, fq, lane, wave,
@@ -1154,17 +1199,17 @@ __global__ __launch_bounds__(512, 1) void k_linear_dma8(int M, int N, int K, con
 
 // MT x NT tiles of (32 WTA) x (64 WT) on the 8-wave tile with an LDS ring of NST stages: for launches with
 // no more tiles than CUs, where each workgroup's K loop waits on load latency rather than on the matrix
-// cores (one candidate's projections, M = 1560).
-template <int EPI, typename TO, int WTA, int WT, int NST>
+// cores (one candidate's projections, M = 1560).  RANGES: K in ranges of `range` tiles, see dma8_tile.
+template <int EPI, typename TO, int WTA, int WT, int NST, bool RANGES>
 __global__ __launch_bounds__(512, 1) void k_linear_deep(int M, int N, int K, const bf16 *__restrict__ A,
                                                  const bf16 *__restrict__ Wt, EpiArgs e, int MT, int NT,
-                                                 int group_m) {
+                                                 int group_m, int range) {
   extern __shared__ __attribute__((aligned(16))) bf16 smem[];
   int mt, nt;
   mf::tile_of(blockIdx.x, MT, NT, mt, nt, group_m);
   const int m0 = 32 * WTA * mt, n0 = 64 * WT * nt;
   if (m0 >= M) return;
-  dma8_tile<EPI, TO, WTA, WT, NST>(M, N, K, A, Wt, e, m0, n0, smem, K);
+  dma8_tile<EPI, TO, WTA, WT, NST, 0, RANGES>(M, N, K, A, Wt, e, m0, n0, smem, K, range);
 }
 
 // Split-K: MT x NT tiles of (32 WTA) x (64 WT) on the 8-wave tile with an LDS ring of NST stages, each
@@ -1945,10 +1990,10 @@ static hipError_t launch_dma8(int M, int N, int K, const void *A, const void *Wt
 }
 
 // The deep-ring 8-wave kernel: (32 WTA) x (64 WT) tiles, NST LDS stages.
-template <int EPI, int WTA, int WT, int NST>
-static hipError_t launch_deep(int M, int N, int K, const void *A, const void *Wt, const EpiArgs &e, hipStream_t s) {
+template <int EPI, int WTA, int WT, int NST, bool RANGES = false>
+static hipError_t launch_deep(int M, int N, int K, const void *A, const void *Wt, const EpiArgs &e, hipStream_t s, int range = 0) {
   const size_t lds = (size_t)NST * (32 * WTA + 64 * WT) * mf::BK * sizeof(bf16);
-  auto kern = k_linear_deep<EPI, bf16, WTA, WT, NST>;
+  auto kern = k_linear_deep<EPI, bf16, WTA, WT, NST, RANGES>;
   static bool attr_set = false;
   if (!attr_set) {
     hipError_t err = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -1957,7 +2002,7 @@ static hipError_t launch_deep(int M, int N, int K, const void *A, const void *Wt
   }
   const int MT = (M + 32 * WTA - 1) / (32 * WTA), NT = (N + 64 * WT - 1) / (64 * WT);
   hipLaunchKernelGGL(kern, dim3(MT * NT), dim3(512), lds, s, M, N, K, (const bf16 *)A, (const bf16 *)Wt, e, MT, NT,
-                     group_rows(NT, K, kDeepGroup));
+                     group_rows(NT, K, kDeepGroup), range);
   return hipGetLastError();
 }
 
@@ -2219,12 +2264,15 @@ int describe_linear(ActType t, int epi, int M, int N, int K, char *buf, int len)
 // candidate's MLP down-projection (M = 1560, N = 1536, K = 8960, residual epilogue; reduction included):
 // 160 x 128 x 2 ranges (240 workgroups) 53 us, against 62 us for 224 x 256 x 5 ranges on two stages,
 // 56 us for 128 x 256 x 3, 60 us for 160 x 256 x 4 and 63 us unsplit (128 x 128, 156 workgroups).  Where
-// the unsplit launch has nearly as many workgroups the partial sums cost more than they give: M = 3120 has 240
-// either way and takes 77 us unsplit, 83 split, so a split has to bring a quarter more.  A
-// function of the shape alone, so every caller with a workspace gets the same plan (and the same bits).
+// the deep-ring tile on the whole of K has nearly as many workgroups, the round trip of the partial sums costs more
+// than it gives: M = 3120 has 240 either way and takes 87.5 us as one launch (85.9 with one sum over K), 79.2 + 13.8
+// split.  So ranges that do not bring a quarter more workgroups are taken one after another by the workgroup of their
+// tile (`serial`), with the same sums.  A function of the shape alone, so every caller with a workspace gets the same
+// plan (and the same bits).
 // FLASHBON_SPLITK (tuning): "<rows>:<cols>:<stages>:<splits>" forces a plan on the shapes that split.
 struct SplitPlan {
   int splits, wta, wt, nst;
+  bool serial = false;
 };
 static SplitPlan splitk_plan(int epi, int M, int N, int K) {
   SplitPlan none = {1, 7, 4, 2};
@@ -2250,16 +2298,22 @@ static SplitPlan splitk_plan(int epi, int M, int N, int K) {
   }
   SplitPlan best = none;
   int64_t most = 0, whole = 0;   // workgroups of the plan, and of the deep-ring tile on the whole of K
+  int wta = 0, wt = 0;           // that tile
   for (const auto &d : kDeepTiles) {
     const int64_t t = (int64_t)((M + 32 * d[0] - 1) / (32 * d[0])) * ((N + 64 * d[1] - 1) / (64 * d[1]));
-    if (t <= cus && t > whole) whole = t;
+    if (t <= cus && t > whole) {
+      whole = t;
+      wta = d[0];
+      wt = d[1];
+    }
     for (int sp = 2; sp <= K / (16 * mf::BK) && t * sp <= cus; ++sp)
       if (usable(sp) && t * sp > most) {
         most = t * sp;
         best = {sp, d[0], d[1], 3};
       }
   }
-  return 4 * most >= 5 * whole ? best : none;
+  if (best.splits > 1 && 4 * most < 5 * whole) best = {best.splits, wta, wt, 3, true};
+  return best;
 }
 
 int splitk_splits(int epi, int M, int N, int K) { return splitk_plan(epi, M, N, K).splits; }
@@ -2282,11 +2336,33 @@ static hipError_t launch_splitk(int M, int N, int K, const void *A, const void *
   return hipGetLastError();
 }
 
+template <int EPI>
+static hipError_t launch_ranges(const SplitPlan &pl, int M, int N, int K, const void *A, const void *Wt, const EpiArgs &e,
+                                hipStream_t s, int range) {
+  switch (10 * pl.wta + pl.wt) {
+    case 42: return launch_deep<EPI, 4, 2, 3, true>(M, N, K, A, Wt, e, s, range);
+    case 52: return launch_deep<EPI, 5, 2, 3, true>(M, N, K, A, Wt, e, s, range);
+    case 44: return launch_deep<EPI, 4, 4, 3, true>(M, N, K, A, Wt, e, s, range);
+    case 54: return launch_deep<EPI, 5, 4, 3, true>(M, N, K, A, Wt, e, s, range);
+    default: return hipErrorInvalidValue;
+  }
+}
+
 hipError_t launch_linear_ws(ActType t, int epi, int M, int N, int K, const void *A, const void *Wt, const EpiArgs &e,
                             hipStream_t s, void *ws, size_t ws_bytes) {
   const SplitPlan pl = t == ACT_BF16 && ws ? splitk_plan(epi, M, N, K) : SplitPlan{1, 7, 4, 2};
   const int sp = pl.splits;
   if (sp < 2 || (size_t)sp * M * N * 4 > ws_bytes) return launch_linear(t, epi, M, N, K, A, Wt, e, s);
+  if (pl.serial) {
+    const int range = (K / mf::BK + sp - 1) / sp;
+    switch (epi) {
+      case EPI_STORE: return launch_ranges<EPI_STORE>(pl, M, N, K, A, Wt, e, s, range);
+      case EPI_GELU: return launch_ranges<EPI_GELU>(pl, M, N, K, A, Wt, e, s, range);
+      case EPI_STORE_F32: return launch_ranges<EPI_STORE_F32>(pl, M, N, K, A, Wt, e, s, range);
+      case EPI_RESIDUAL: return launch_ranges<EPI_RESIDUAL>(pl, M, N, K, A, Wt, e, s, range);
+      default: return hipErrorInvalidValue;
+    }
+  }
   float *part = (float *)ws;
   hipError_t err;
   switch (100 * pl.wta + 10 * pl.wt + pl.nst) {

@@ -33,3 +33,18 @@ def small_draft():
 
 def test_small_draft():
     assert small_draft() == "cef9235cb4c7a7b4"
+
+
+def guided_refine():
+    """Two token rows of 1560 tokens at the 1.3B layer shapes: the MLP down-projection's K ranges are taken in turn."""
+    shape = dataclasses.replace(synth.WORKLOADS["wan1.3b_step"].shape, num_blocks=1, qk_norm_rope=True)
+    wl = dataclasses.replace(synth.WORKLOADS["wan1.3b_step"], shape=shape, text_len=64)
+    pool = DraftPool(wl, weights=synth.make_weights(shape, 6)[0], guidance=5.0)
+    pool.reset()
+    for k in range(2):
+        pool.refine_step(25 + k)
+    return _digest(pool.latents)
+
+
+def test_guided_refine():
+    assert guided_refine() == "4371aea17c72dbbe"
