@@ -765,7 +765,7 @@ static hipError_t launch_f32_dh(const AttnP &p, hipStream_t s) {
 }
 
 // Whether k_attn_f32 takes the call: K, V and the output in whole 16-byte pieces (bf16 outputs in 8-byte
-// ones), key rows whose offsets within a tile fit 31 bits, and a grid that does.
+// ones), key rows whose offsets within a tile fit 31 bits, and a grid of fewer than 2^32 threads in x.
 template <typename T>
 static bool f32_takes(const AttnP &p) {
   const char *force = getenv("FLASHBON_ATTN_F32");
@@ -773,7 +773,7 @@ static bool f32_takes(const AttnP &p) {
   const int64_t piece = 16 / sizeof(T), opiece = 4;
   return ((uintptr_t)p.k | (uintptr_t)p.v) % 16 == 0 && p.kv_bs % piece == 0 && p.kv_rs % piece == 0 && p.kv_rs >= 0 &&
          p.kv_rs <= 1 << 21 && (uintptr_t)p.out % (opiece * sizeof(T)) == 0 && p.o_bs % opiece == 0 && p.o_rs % opiece == 0 &&
-         (int64_t)p.batch * p.heads * ((p.tq + 31) / 32) < (int64_t)1 << 31;
+         (int64_t)p.batch * p.heads * ((p.tq + 31) / 32) < (int64_t)1 << 24;
 }
 
 template <typename T>
