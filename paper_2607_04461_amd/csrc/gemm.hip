@@ -2068,6 +2068,7 @@ static F32Tile f32_tile(int M, int N, int K, bool aligned) {
   const int cus = cu_count();
   auto tiles = [&](int64_t t) { return (M + t - 1) / t * ((N + t - 1) / t); };
   if (K <= 64 && tiles(16) <= cus) return F32_DOT;
+  if (tiles(32) >= (int64_t)1 << 24) return F32_MID;   // 2^32 threads in x
   return 1.15 * (double)tiles(32) / (4 * cus) < (double)((tiles(64) + cus - 1) / cus) ? F32_SMALL : F32_MID;
 }
 

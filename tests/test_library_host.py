@@ -250,6 +250,14 @@ def test_linear_plan_of_model_shapes(shape, kernels, desc, monkeypatch):
         assert shape[0] <= total < shape[0] + lo
 
 
+@pytest.mark.parametrize("M,N,tile", [(2 ** 29 - 32, 4, "32x32"), (2 ** 29, 4, "64x64"), (2 ** 28, 36, "64x64"),
+                                      (2 ** 30 - 64, 32, "64x64")])
+def test_fp32_plan_stays_within_a_launch(M, N, tile, monkeypatch):
+    """256 threads a tile: at most 2^24 - 1 tiles, beyond which 32x32 tiles give way to 64x64."""
+    monkeypatch.delenv("FLASHBON_LINEAR_TILE", raising=False)
+    assert fb.flashbon_op_linear_plan(fb.FP32, M, N, 8, 0)[1].startswith("k_linear_f32: " + tile)
+
+
 def test_linear_plan_follows_override_and_rejects_bad_arguments(monkeypatch):
     monkeypatch.setenv("FLASHBON_LINEAR_TILE", "split:24320")
     n, d = fb.flashbon_op_linear_plan(fb.BF16, 24960, 8960, 1536, 1)
