@@ -61,7 +61,8 @@ flashbon_status flashbon_op_linear_ws(int32_t dtype, int32_t M, int32_t N, int32
  * a NUL-terminated one-line description of the kernels and tiles (truncated to desc_len - 1
  * characters; desc may be NULL).  Same argument rules as flashbon_op_linear; follows the
  * FLASHBON_LINEAR_TILE override like the launch does.  The plan depends on the device's CU count
- * (256 when no device is visible). */
+ * (256 when no device is visible), and for FP32 on buffers that start on 16 bytes (others run on the vector
+ * ALUs, with the same sums). */
 flashbon_status flashbon_op_linear_plan(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t epilogue,
                                         int32_t *kernels, char *desc, int32_t desc_len);
 

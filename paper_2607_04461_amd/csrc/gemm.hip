@@ -2212,9 +2212,7 @@ int describe_linear(ActType t, int epi, int M, int N, int K, char *buf, int len)
   std::string d;
   int kernels = 1;
   auto rows_of = [](int w) { return std::to_string(32 * w); };
-  if (t == ACT_BF16 && epi == EPI_EULER) {
-    d = "k_linear_narrow or k_linear_deep with the latent update";
-  } else if (t != ACT_BF16) {
+  if (t != ACT_BF16) {
     switch (f32_tile(M, N, K, true)) {   // operands on 16 bytes
       case F32_MID: d = "k_linear_f32: 64x64 tiles, fp32 matrix cores"; break;
       case F32_SMALL: d = "k_linear_f32: 32x32 tiles, K over 4 waves, fp32 matrix cores"; break;
@@ -2337,6 +2335,8 @@ static hipError_t launch_splitk(int M, int N, int K, const void *A, const void *
   return hipGetLastError();
 }
 
+// A serial plan's tile fills more than 0.8 of the CUs while some tile fills at most half of them: never 160 x 256,
+// of which a layer has the fewest.
 template <int EPI>
 static hipError_t launch_ranges(const SplitPlan &pl, int M, int N, int K, const void *A, const void *Wt, const EpiArgs &e,
                                 hipStream_t s, int range) {
@@ -2344,7 +2344,6 @@ static hipError_t launch_ranges(const SplitPlan &pl, int M, int N, int K, const 
     case 42: return launch_deep<EPI, 4, 2, 3, true>(M, N, K, A, Wt, e, s, range);
     case 52: return launch_deep<EPI, 5, 2, 3, true>(M, N, K, A, Wt, e, s, range);
     case 44: return launch_deep<EPI, 4, 4, 3, true>(M, N, K, A, Wt, e, s, range);
-    case 54: return launch_deep<EPI, 5, 4, 3, true>(M, N, K, A, Wt, e, s, range);
     default: return hipErrorInvalidValue;
   }
 }
