@@ -54,13 +54,14 @@ def _run(dtype, batch, heads, dh, tq, tk, cross, **kw):
     return out.clone()
 
 
-@pytest.mark.parametrize("slabs", ["1", "2", "4"])
+@pytest.mark.parametrize("slabs", ["1", "2", "4", "valu"])
 @pytest.mark.parametrize("dtype,dh", [("fp32", 8), ("fp32", 16), ("fp32", 32), ("fp32", 64), ("fp32", 128),
                                       ("bf16", 8), ("bf16", 16), ("bf16", 32), ("bf16", 64)])
 @pytest.mark.parametrize("tq,tk,cross", [(1, 1, False), (31, 7, True), (33, 33, False), (64, 65, True), (129, 128, True),
                                          (40, 257, True)])
 def test_each_split(slabs, dtype, dh, tq, tk, cross, monkeypatch):
-    """One key, keys and queries beside the tiles of 32, 64 and 128, slabs wholly past the last key."""
+    """One key, keys and queries beside the tiles of 32, 64 and 128 (of 16 and 64 for the vector-ALU kernel that takes
+    the calls this one does not), slabs wholly past the last key."""
     monkeypatch.setenv("FLASHBON_ATTN_F32", slabs)
     _run(dtype, 3, 3, dh, tq, tk, cross)
 
@@ -74,6 +75,16 @@ def test_strides_and_addresses(dtype, gap, offset, monkeypatch):
     if gap % 4 or offset:
         monkeypatch.setenv("FLASHBON_ATTN_F32", "valu")
         assert torch.equal(out, _run(dtype, 2, 3, 32, 50, 70, True, gap=gap, offset=offset))
+
+
+@pytest.mark.parametrize("dtype,dh", [("fp32", 8), ("fp32", 64), ("fp32", 128), ("bf16", 16), ("bf16", 64)])
+@pytest.mark.parametrize("tq,tk", [(1, 1), (65, 47), (64, 16), (70, 33)])
+def test_misaligned_rows(dtype, dh, tq, tk, monkeypatch):
+    """The dispatch's own choice for rows that start off 16 bytes: the vector-ALU kernel at every head dim."""
+    monkeypatch.delenv("FLASHBON_ATTN_F32", raising=False)
+    out = _run(dtype, 2, 3, dh, tq, tk, True, gap=2, offset=2)
+    monkeypatch.setenv("FLASHBON_ATTN_F32", "valu")
+    assert torch.equal(out, _run(dtype, 2, 3, dh, tq, tk, True, gap=2, offset=2))
 
 
 @pytest.mark.parametrize("slabs", ["1", "2", "4"])
