@@ -6,16 +6,18 @@
 //     plans; k_linear_mfma<8,4,2,4>: 8 waves of 128x64 with register-staged loads for other K) or
 //     128x128 (4 waves of 64x64, two workgroups per CU), chosen per shape by a round-count model;
 //     k_linear_deep: the 8-wave tile at 128 or 160 rows x 128 or 256 columns with a three-stage LDS
-//     ring, for launches that fit one round of workgroups one per CU (one or two candidates); K
+//     ring, for launches that fit one round of workgroups one per CU (one or two candidates);
+//     k_linear_narrow: 32x64 tiles for layers of at most one such tile per CU; K
 //     tiles of 64 in double-buffered, XOR-swizzled LDS; XCD-aware grouped tile order.  Operands are swapped (the weight tile feeds the MFMA "A" side) and the weight rows
-//     permuted so that every lane owns 8 consecutive output columns of one row.  Every kernel
-//     accumulates K in the same order, so an output element does not depend on the tiling.  The
+//     permuted so that every lane owns 8 consecutive output columns of one row (four in k_linear_narrow).
+//     Every one of them accumulates K in the same order, so an output element does not depend on the
+//     tiling; split-K launches add K ranges that the shape alone sets.  The
 //     8-wave tiles' epilogues (bf16 store and GELU of 256-column tiles, residual updates, split-K
 //     partial sums) pass each wave's block through the freed LDS ring so that every global access
 //     covers whole 128-byte rows.
 //   * k_linear_f32: fp32 operands on the matrix cores (v_mfma_f32_32x32x2_f32), 64x64 tiles or 32x32 tiles
 //     with K shared by four waves; k_linear_valu_dot for the shortest sums and k_linear_valu (64x64 tiles,
-//     vector ALUs) for buffers that are not on 16 bytes.
+//     vector ALUs) for buffers that are not on 16 bytes.  All four sum K in one order of their own.
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -1828,9 +1830,11 @@ static TileChoice pick_tiles(int M, int N, int K, bool dma_ok) {
     return {strcmp(force, "128x128") ? PLAN_BIG : PLAN_SMALL, 8, 0, 0, 0};
   }
   // At most one 32x64 tile a CU: k_linear_narrow.  Against 128x128 tiles (the K >= 128 shapes, us): (390, 256, 256)
-  // 4.2 and 5.5, (390, 704, 256) 4.2 and 5.8, (390, 256, 704) 6.5 and 7.8, (16, 8960, 1536) 10.2 and 12.3,
-  // (256, 1536, 1536) 11.9 and 12.2; beyond it falls back ((390, 1536, 256), 312 tiles, 6.0 and 5.8; (256, 4608,
-  // 1536), 576 tiles, 30 and 13).
+  // 3.5 and 5.6, (390, 704, 256) 3.6 and 5.7, (390, 256, 704) 5.2 and 7.9, (16, 8960, 1536) 7.9 and 12.6,
+  // (256, 1536, 1536) 9.2 and 12.2, (8000, 64, 1536), 250 tiles, 8.6 and 12.4; beyond it a second round falls back
+  // but for the shortest sums ((10000, 64, 1536), 313 tiles, 14.3 and 12.8; (600, 1024, 1024), 304 tiles, 10.5 and
+  // 9.6; (390, 2048, 704), 416 tiles, 9.4 and 8.5; (256, 4608, 1536), 576 tiles, 24 and 13; (390, 1536, 256), 312
+  // tiles, 5.4 and 5.8).
   if (narrow_fits(M, N, K)) return {PLAN_NARROW, 0, 0, 0, 0, 8};
   constexpr double kSmallA = 0.704, kSmallFix = 604.0;
   const int cus = cu_count();
@@ -1933,8 +1937,9 @@ static hipError_t launch_mfma(int M, int N, int K, const void *A, const void *Wt
 //
 // Launches of one round have orders of their own, all their tiles being at work at once: groups of 5 row blocks
 // for the deep-ring tile ((1560, 1536, 1536) 13.9 us, 14.5 at 8 and 15.1 at 1; (3120, 1536, 8960) 77.0, 77.4 and
-// 77.7), groups of 3 for split-K ((1560, 1536, 8960) 49.0 us, 49.7 at 1 and 49.2 at 8; (500, 5120, 13824) 71.9, 83.2
-// and 69.7; (512, 1536, 4096) 17.3, 17.3 and 19.8).
+// 77.7), groups of 3 for split-K, a compromise that 8 beats at the 14B shape by 3% and that beats 8 by 13% at the text
+// projection's ((1560, 1536, 8960) 49.0 us, 49.7 at 1 and 49.2 at 8; (500, 5120, 13824) 71.9, 83.2 and 69.7;
+// (512, 1536, 4096) 17.3, 17.3 and 19.8).
 constexpr int kDeepGroup = 5, kSplitGroup = 3;
 static int group_rows(int NT, int K, int otherwise = 0) {
   const char *force = getenv("FLASHBON_LINEAR_GROUP");
@@ -2151,9 +2156,9 @@ static hipError_t launch_epi(ActType t, int M, int N, int K, const void *A, cons
                              const EpiArgs &e, hipStream_t s) {
   if (t == ACT_BF16) {
     if constexpr (EPI == EPI_EULER) {
-      // the head: its columns are one tile wide, so past one 32x64 tile a CU the 128x128 tile's whole-row loads
-      // stream A better (24960 rows of K = 1536: 28 us against 44;
-      // 58 on 128x128 tiles with four divisions an output)
+      // the head: its columns are one tile wide, so past one 32x64 tile a CU (a second round of those) 128x128 tiles
+      // stream A better (fp32 store at K = 1536, us: 8000 rows 8.6 on 32x64 tiles and 12.4, 10000 rows 14.3 and 12.8,
+      // 24960 rows 27.8 and 16.3; with the latent update 28 at 24960 rows)
       const bool dma_ok = K % mf::BK == 0 && K >= 2 * mf::BK && N % 8 == 0;
       if (dma_ok && !narrow_fits(M, N, K)) return launch_deep<EPI, 4, 2, 3>(M, N, K, A, Wt, e, s);
       return launch_narrow<EPI>(M, N, K, A, Wt, e, s);
@@ -2178,19 +2183,21 @@ static hipError_t launch_epi(ActType t, int M, int N, int K, const void *A, cons
   return hipGetLastError();
 }
 
-// adaLN rows that the next layer's kernel can make for itself, for less than a launch costs (bf16, 390 rows of 256:
-// 6.4 us against 4.2 for the layer and 3.5 for k_ln_mod; 32 rows of 64 3.6 against 2.1 and 3.0; and a launch
-// less on the host, which such steps wait for): layers that k_linear_narrow takes (rows of at
-// most 1024, whose 32 fit LDS beside nothing else) or, in fp32, k_linear_valu_dot.  A forced tile takes the layer alone.
+// adaLN rows that the next layer's kernel can make for itself, for no more than the two launches take on the device
+// and a launch less on the host, which such steps wait for: layers that k_linear_narrow takes with rows of at most 512,
+// or, in fp32, k_linear_valu_dot.  The four layers of a step that read such rows, us together, fused and as two
+// launches each: bf16, 390 rows of 256 22 and 28, of 288 26 and 30, of 384 30 and 31; 130 rows of 512 32 and 32, 126
+// of 1024 52 and 42 (16 pieces a lane, each with its modulation to wait for); fp32, 32 rows of 64 17 and 26.  A forced
+// tile takes the layer alone.
 bool ln_linear_takes(ActType t, int M, int N, int D) {
   if (getenv("FLASHBON_LINEAR_TILE")) return false;
-  return t == ACT_BF16 ? D <= 1024 && narrow_fits(M, N, D) : f32_tile(M, N, D, true) == F32_DOT;
+  return t == ACT_BF16 ? D <= 512 && narrow_fits(M, N, D) : f32_tile(M, N, D, true) == F32_DOT;
 }
 
 template <int EPI>
 static hipError_t ln_linear(ActType t, int M, int N, int D, const LnArgs &ln, const void *Wt, const EpiArgs &e, hipStream_t s) {
   if (t == ACT_BF16) {
-    return D <= 256 ? launch_narrow_ln<EPI, 4>(M, N, D, nullptr, Wt, e, ln, s) : launch_narrow_ln<EPI, 16>(M, N, D, nullptr, Wt, e, ln, s);
+    return D <= 256 ? launch_narrow_ln<EPI, 4>(M, N, D, nullptr, Wt, e, ln, s) : launch_narrow_ln<EPI, 8>(M, N, D, nullptr, Wt, e, ln, s);
   }
   hipLaunchKernelGGL((k_linear_valu_dot<EPI, true>), dim3((M + 15) / 16, (N + 15) / 16), dim3(256), 0, s, M, N, D, nullptr,
                      (const float *)Wt, e, ln);
@@ -2266,7 +2273,9 @@ int describe_linear(ActType t, int epi, int M, int N, int K, char *buf, int len)
 // the deep-ring tile on the whole of K has nearly as many workgroups, the round trip of the partial sums costs more
 // than it gives: M = 3120 has 240 either way and takes 87.5 us as one launch (85.9 with one sum over K), 79.2 + 13.8
 // split.  So ranges that do not bring a quarter more workgroups are taken one after another by the workgroup of their
-// tile (`serial`), with the same sums.  A function of the shape alone, so every caller with a workspace gets the same
+// tile (`serial`), with the same sums.  Layers of few rows, whole on k_linear_narrow: (16, 1536, 8960) 16.1 us split
+// and 30.0 whole, (38, 5120, 13824) 29.6 and 47.5, (16, 1536, 4096) 14.6 and 15.4; at (64, 2560, 2560) the split takes
+// 13.6 against 10.9 and is kept for its sums.  A function of the shape alone, so every caller with a workspace gets the same
 // plan (and the same bits).
 // FLASHBON_SPLITK (tuning): "<rows>:<cols>:<stages>:<splits>" forces a plan on the shapes that split.
 struct SplitPlan {

@@ -12,10 +12,10 @@ from paper_2607_04461_amd.pool import DraftPool
 pytestmark = pytest.mark.gpu
 
 
-# hidden widths on both sides of the fused rows' 256 (4 and 16 pieces a lane, whole and partial ones) and the fp32
-# rows' 64; 1040 is wider than rows that are fused
+# hidden widths on both sides of the fused rows' 256 (4 and 8 pieces a lane, whole and partial ones) and the fp32
+# rows' 64; 544, 1024 and 1040 are wider than rows that are fused
 @pytest.mark.parametrize("dtype,hidden,heads", [("bf16", 64, 4), ("bf16", 96, 3), ("bf16", 256, 2), ("bf16", 288, 9),
-                                                ("bf16", 1024, 8), ("bf16", 1040, 65), ("fp32", 8, 1), ("fp32", 40, 5),
+                                                ("bf16", 512, 4), ("bf16", 544, 17), ("bf16", 1024, 8), ("bf16", 1040, 65), ("fp32", 8, 1), ("fp32", 40, 5),
                                                 ("fp32", 64, 4)])
 @pytest.mark.parametrize("guidance", [None, 3.0])
 def test_same_bits(dtype, hidden, heads, guidance):
