@@ -1779,7 +1779,8 @@ static constexpr double kF[9] = {0, 0, 0, 0, 0, 0.79, 0.82, 0.85, 1.0};
 static constexpr double kF8[9] = {0, 0, 0, 0, 0, 0.78, 0.826, 0.885, 1.0};
 static constexpr double kSmall8 = 1.064, kMixGain8 = 0.01;
 static constexpr double kG = 130.0, kMixGain = 0.02;
-static TileChoice pick_tiles(int M, int N, int K, bool dma_ok) {
+// aligned: operands on 16 bytes, which k_linear_narrow's loads into LDS take; others keep the tiles of larger layers.
+static TileChoice pick_tiles(int M, int N, int K, bool dma_ok, bool aligned = true) {
   // FLASHBON_LINEAR_TILE (tests and tuning): "256x256", "128x128", "bm:<rows>" (4-wave kernel, one
   // tile height: rows 160, 192 or 224), "mix:<w>:<blocks>:<tall>" (4-wave kernel, `blocks` row blocks,
   // `tall` of them 32 w rows high and the rest 32 (w - 1), w in 6..8, covering M), or
@@ -1789,7 +1790,7 @@ static TileChoice pick_tiles(int M, int N, int K, bool dma_ok) {
   // (k_linear_deep: rows 128 or 160, cols 128 or 256, 2 or 3 LDS stages)
   const char *force = getenv("FLASHBON_LINEAR_TILE");
   if (force) {
-    if (!strcmp(force, "narrow")) return {PLAN_NARROW, 0, 0, 0, 0, 8};
+    if (aligned && !strcmp(force, "narrow")) return {PLAN_NARROW, 0, 0, 0, 0, 8};
     if (dma_ok && !strncmp(force, "deep:", 5)) {
       int rows = 0, cols = 0, nst = 0;
       if (sscanf(force + 5, "%d:%d:%d", &rows, &cols, &nst) == 3 && deep_ok(rows / 32, cols / 64, nst) &&
@@ -1835,7 +1836,7 @@ static TileChoice pick_tiles(int M, int N, int K, bool dma_ok) {
   // but for the shortest sums ((10000, 64, 1536), 313 tiles, 14.3 and 12.8; (600, 1024, 1024), 304 tiles, 10.5 and
   // 9.6; (390, 2048, 704), 416 tiles, 9.4 and 8.5; (256, 4608, 1536), 576 tiles, 24 and 13; (390, 1536, 256), 312
   // tiles, 5.4 and 5.8).
-  if (narrow_fits(M, N, K)) return {PLAN_NARROW, 0, 0, 0, 0, 8};
+  if (aligned && narrow_fits(M, N, K)) return {PLAN_NARROW, 0, 0, 0, 0, 8};
   constexpr double kSmallA = 0.704, kSmallFix = 604.0;
   const int cus = cu_count();
   auto rounds = [&](int64_t tiles, int per_cu) { return (double)((tiles + per_cu * cus - 1) / (per_cu * cus)); };
@@ -2117,7 +2118,7 @@ static hipError_t launch_narrow(int M, int N, int K, const void *A, const void *
 template <int EPI>
 static hipError_t launch_bf16(int M, int N, int K, const void *A, const void *Wt, const EpiArgs &e, hipStream_t s) {
   const bool dma_ok = K % mf::BK == 0 && K >= 2 * mf::BK && N % 8 == 0;
-  const TileChoice c = pick_tiles(M, N, K, dma_ok);
+  const TileChoice c = pick_tiles(M, N, K, dma_ok, ((uintptr_t)A | (uintptr_t)Wt) % 16 == 0);
   if (c.plan == PLAN_NARROW) return launch_narrow<EPI>(M, N, K, A, Wt, e, s);
   if (c.plan == PLAN_SMALL) return launch_mfma<4, 4, 2, 2, EPI, 2>(M, N, K, A, Wt, e, s);
   if (c.plan == PLAN_BIG) return launch_big<EPI>(M, N, K, A, Wt, e, s);

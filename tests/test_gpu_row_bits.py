@@ -68,6 +68,19 @@ def test_rows(dtype, N, K, epi, monkeypatch):
         assert torch.equal(o, outs[0])
 
 
+# layers of few tiles whose operands start off 16 bytes: half a K tile and a tail, columns in fours
+@pytest.mark.parametrize("M,N,K", [(33, 68, 96), (40, 24, 72), (20, 36, 256)])
+@pytest.mark.parametrize("dtype", list(TILES))
+def test_operands_off_16_bytes(dtype, M, N, K, monkeypatch):
+    monkeypatch.delenv("FLASHBON_LINEAR_TILE", raising=False)
+    a, w, bias, gate, h = _operands(dtype, M, N, K)
+    skip = 8 // a.element_size()
+    off = [torch.cat([x.new_zeros(skip), x.flatten()])[skip:].view(x.shape) for x in (a, w)]
+    assert all(x.data_ptr() % 16 == 8 for x in off)
+    for epi in ("store", "residual"):
+        assert torch.equal(_layer(dtype, *off, bias, gate, h, epi), _layer(dtype, a, w, bias, gate, h, epi))
+
+
 # one candidate alone and in pools of 2 and 7: the head (and with small widths every layer) changes its kernel, and
 # 2 heads of 1369 tokens would each be split differently between the waves of a workgroup
 @pytest.mark.parametrize("dtype,hidden,heads", [("bf16", 128, 1), ("bf16", 128, 2), ("bf16", 64, 4), ("fp32", 256, 2),
