@@ -2105,7 +2105,9 @@ static hipError_t launch_narrow_ln(int M, int N, int K, const void *A, const voi
     attr_set = true;
   }
   const dim3 grid((M + nar::BM - 1) / nar::BM, (N + nar::BN - 1) / nar::BN);
-  hipLaunchKernelGGL(kern, grid, dim3(64 * nar::WAVES), nar::LDS<LN>, s, M, N, K, (const bf16 *)A, (const bf16 *)Wt, e, ln);
+  // a K shorter than the ring leaves the rest of it to other workgroups (K = 256: 48 of 144 KB)
+  const int stages = std::min(nar::NST<LN>, (K + 2 * mf::BK - 1) / (2 * mf::BK));
+  hipLaunchKernelGGL(kern, grid, dim3(64 * nar::WAVES), nar::ROWS<LN> + stages * 2 * nar::HALF<LN>, s, M, N, K, (const bf16 *)A, (const bf16 *)Wt, e, ln);
   return hipGetLastError();
 }
 
