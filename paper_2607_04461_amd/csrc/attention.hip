@@ -130,8 +130,9 @@ constexpr int K_OFF = 0, V_OFF = 2 * TILE_B;
 // XCD-aware: workgroups go to the 8 XCDs round-robin by id, so id -> (unit u = head * batch + candidate,
 // query block) keeps every query block of a unit on XCD u % 8, where its K and V stay in that XCD's L2.
 // A wave in phase B, whose MFMAs wait on nothing but V fragments already read, goes ahead of the other wave of
-// its SIMD (s_setprio), which keeps the two waves in opposite phases: 16 x 12 heads of 1560 x 1560 258 -> 251
-// us, 4 x 12 heads of 4096 x 4096 373 -> 361 (phase A ahead: 256 and 366; both: 259 and 374).  With at most 8 key
+// its SIMD (s_setprio), which keeps the two waves in opposite phases: 16 x 12 heads of 1560 x 1560 252 -> 247
+// us, 4 x 12 heads of 4096 x 4096 361 -> 351 (on another box 258 -> 251 and 373 -> 361; phase A ahead there 256 and
+// 366, both 259 and 374).  With at most 8 key
 // tiles (cross-attention) it gains nothing (100 -> 101 us) and is left out.
 // The normalised output leaves through LDS (the rings are free after a last barrier): a lane holds
 // 16-byte pieces of one query row, so direct stores would write every 128-byte line of the output in
@@ -434,8 +435,8 @@ __global__ __launch_bounds__(256, 2) void k_attn_fa(AttnP p) {
 // themselves) while the other one is worked on, two barriers a tile; two workgroups share a CU.  The
 // exponentials of tile j stand between the MFMAs of S(j + 1), the maxima of S(j + 1) between those of
 // O += V(j) P(j).  Bound by the matrix cores (157 TFLOP/s nominal): at 8 x 16 heads of 2048 x 2048 and head
-// dim 128 they are busy 81% of the cycles (115 TFLOP/s, at 2.15 GHz); 4 x 12 heads of 1560 x 512 take 189 us
-// and 12 heads of 1560 x 1560 229, where k_attn_valu takes 3207 and 4927; bf16, 4 x 16 heads of 1560 x 1560
+// dim 128 they are busy 81% of the cycles (115 TFLOP/s, at 2.15 GHz); 4 x 12 heads of 1560 x 512 take 190 us
+// (103 TFLOP/s) and 12 heads of 1560 x 1560 235, where k_attn_valu takes 3207 and 4927; bf16, 4 x 16 heads of 1560 x 1560
 // and head dim 64, 410 against 2049.
 namespace af {
 constexpr int OUT_OF_RANGE = (int)0x80000000u;

@@ -143,7 +143,7 @@ def test_linear_tile_plans_bit_identical(epi, monkeypatch):
     for tile in ["256x256", "128x128", "split:512", "bm:224", "bm:192", "bm:160", "mix:7:6:1", "mix:8:5:1",
                  "mix:6:7:3", "w8", "w8:bm:224", "w8:bm:192", "w8:bm:160", "w8:mix:7:6:1", "w8:mix:6:7:3",
                  "deep:128:128:2", "deep:128:128:3", "deep:160:128:2", "deep:160:128:3", "deep:128:256:2",
-                 "deep:128:256:3", "deep:160:256:2", "deep:160:256:3"]:
+                 "deep:128:256:3", "deep:160:256:2", "deep:160:256:3", "narrow"]:
         monkeypatch.setenv("FLASHBON_LINEAR_TILE", tile)
         if epi == "store":
             out = torch.empty((M, N), device="cuda", dtype=torch.float32)
