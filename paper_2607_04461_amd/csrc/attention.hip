@@ -738,6 +738,7 @@ static int attn_slabs(const AttnP &p, int dh) {
   // FLASHBON_ATTN_F32 (tests and tuning): "valu" or the number of slabs
   const char *force = getenv("FLASHBON_ATTN_F32");
   if (force && (atoi(force) == 1 || atoi(force) == 2 || atoi(force) == 4)) return atoi(force);
+  if (p.tk <= 32) return 1;   // one slab of keys
   const int cus = cu_count();
   const double mfma = (dh / 2 + 16.0 * (dh < 32 ? 1 : dh / 32)) / 128 + (dh < 128 ? 0.06 : 0.0);
   auto cost = [&](int batch, int slabs, double tile, double fixed) {
